@@ -1242,3 +1242,27 @@ def test_side_stream_outside_stream_context(sf):
     np.testing.assert_array_equal(i2.cpu().numpy(), oi)
     np.testing.assert_array_equal(l2.cpu().numpy(), ol)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("window", [31, 32, 33, 63, 65, 127, 255, 511, 1023, 2047, 2049, 4095, 4096, 4097])
+def test_median_tile_edges(sf, window):
+    """The tiled select at the edges of its shapes: windows around every
+    tile height, column counts C = S * R of one, two, and one more or less
+    than every tile width (8 to 256 columns), odd C (8-byte aligned pairs),
+    and columns whose median lies on either side of 2^32 - 1, where the
+    32-bit tile saturates, or that hold ties, zeros or one far value."""
+    rng = np.random.Generator(np.random.PCG64(window))
+    T = window + window // 3 + 1                 # a ragged last window
+    for S, R in ((1, 1), (1, 2), (3, 1), (1, 31), (3, 11), (5, 13), (1, 127), (2, 129), (1, 257)):
+        if T * S * R > 1 << 20:
+            R = 17
+        d = rng.lognormal(17.0, 0.1, size=(T, S, R)).astype(np.int64)
+        d[:, 0, 0] = (1 << 32) - 2 + rng.integers(0, 3, size=T)        # medians around saturation
+        d[:, S - 1, R - 1] = (1 << 32) + rng.integers(-9, 1 << 20, size=T)
+        if R > 4:
+            d[:, 0, 1] = 40_000_000                                    # constant
+            d[:, 0, 2] = 1000 * rng.integers(0, 3, size=T)             # mass ties and zeros
+            d[::7, 0, 3] *= 4000                                       # one in seven past 2^32
+            d[:, 0, 4] = rng.integers(0, 1 << 47, size=T)              # wide
+        print("case window=%d T=%d S=%d R=%d" % (window, T, S, R), flush=True)
+        assert_median_equal(sf, d, window)
