@@ -574,7 +574,7 @@ def main() -> int:
             wm = float(g_out["window_makespan"].sum())
             next_rows["exposure_gain"] = {
                 "kernel": ("k_exposure_gain_near (+ k_window_sum)"
-                           if S <= 16 and 4096 < R <= 16384 and R % 2 == 0
+                           if S >= 9 and 128 < R <= 32768
                            else "k_exposure_gain (+ k_window_sum)"),
                 "bound": "hbm",
                 "launch_ms": g_ms,

@@ -209,16 +209,13 @@ int sf_route(const int64_t* stage_exposed, int64_t W, int32_t S, int64_t tau_num
  *   baseline             [W][S][R] int64 ns: btilde for the steps of window
  *                        w (a per-rank window median, a cohort median, a
  *                        no-stall reference, ...).
- *   T, R, S, window      as for sf_window_summary.  Up to 64 stages the
- *                        per-stage deltas are held in registers and the
- *                        durations read once; past 64 a two-pass kernel
- *                        reads each step's durations twice (slower, same
- *                        results).  From 4097 to 16384 ranks (up to 16
- *                        stages, even R, 16-byte aligned inputs) a step's
- *                        durations are read once into rank totals and the
- *                        baseline only for the ranks near the frontier; a
- *                        step that the bound does not settle is read again
- *                        over all ranks (same results).
+ *   T, R, S, window      as for sf_window_summary.  Short steps keep their
+ *                        per-stage deltas in registers (up to 24 stages) or
+ *                        make two passes over each step's durations; long
+ *                        ones (up to 32768 ranks and 4096 stages) read the
+ *                        durations once into rank totals and the baseline
+ *                        only for the ranks that can still hold a stage's
+ *                        maximum.  Same results.
  *   out_gain             [T][S] int64: the gain of each step and stage.
  *   out_makespan         [T] int64: F[t][S-1], the step's exposed makespan.
  *   out_window_gain      [W][S] int64: window sums of out_gain.

@@ -11,9 +11,10 @@
 // reduces once per step; otherwise the group reduces every tile.  Partial
 // maxima of several groups meet in LDS.
 //
-// Past 4096 ranks (up to 16384, 16 stages) k_exposure_gain_near takes the
-// maximum over the ranks near the frontier first and over all ranks only
-// when a bound requires it.
+// Long steps (use_near) take k_exposure_gain_near, which reads the durations
+// once into rank totals and the baseline for the few ranks near the frontier
+// only; a handful of ranks, or more stages than registers hold, take the
+// two-pass k_exposure_gain_wide.
 
 #include "sf_device.h"
 #include "sf_host.h"
@@ -21,16 +22,16 @@
 
 namespace sfk {
 
-template <int VEC, int K, int G, int WG, int SMAX, bool RUN>
+template <int K, int G, int WG, int SMAX, bool RUN>
 __global__ __launch_bounds__(WG) void k_exposure_gain(
     const int64_t* __restrict__ d, const int64_t* __restrict__ btilde, int64_t T, int R, int S,
     int64_t window, int64_t* __restrict__ gain, int64_t* __restrict__ makespan)
 {
-    static_assert(K % VEC == 0 && (WG % G == 0 || G == WG), "shape");
+    static_assert(K % 2 == 0 && (WG % G == 0 || G == WG), "shape");
     constexpr int SUB = G < 64 ? G : 64;
     constexpr int SPW = WG / G;
     constexpr int SPS = G / SUB;
-    constexpr int NLD = K / VEC;
+    constexpr int NLD = K / 2;
     constexpr int RT = G * K;
     constexpr int NCOL = SMAX + 1;  // SMAX replaced-stage maxima, then F
     static_assert(!RUN || SMAX <= 16, "running maxima of up to 16 stages");
@@ -54,38 +55,40 @@ __global__ __launch_bounds__(WG) void k_exposure_gain(
             int idx[NLD];
 #pragma unroll
             for (int l = 0; l < NLD; ++l) {
-                const int r = r0 + (l * G + gl) * VEC;
-                idx[l] = r < R ? r : r0;
+                // R >= 2: with odd R the last pair overlaps the one before;
+                // a pair past R re-reads the tile's first ranks (the last
+                // pair instead ran 20% slower at 64 ranks)
+                const int r = r0 + (l * G + gl) * 2;
+                idx[l] = min(r < R ? r : r0, R - 2);
             }
             int64_t tot[K];
             int64_t dl[K][SMAX];
 #pragma unroll
             for (int k = 0; k < K; ++k) tot[k] = 0;
+            // the tile's loads all in flight before any is used: left to the
+            // compiler, it waits for the first ones in between to save
+            // registers (64 ranks x 6 stages: 237 us against 187 per 0.8 GB;
+            // with 12 stages or running maxima it is 2-3% faster that way)
+            v2i64_a8 x[SMAX][NLD], y[SMAX][NLD];
 #pragma unroll
             for (int s = 0; s < SMAX; ++s) {
                 const int sr = s < S ? s : 0;
-                const int64_t* row = dt + (int64_t)sr * R;
-                const int64_t* brow = bw + (int64_t)sr * R;
 #pragma unroll
                 for (int l = 0; l < NLD; ++l) {
-                    int64_t x[VEC], y[VEC];
-                    if (VEC == 2) {
-                        const v2i64 a = __builtin_nontemporal_load(reinterpret_cast<const v2i64*>(row + idx[l]));
-                        const v2i64 b = *reinterpret_cast<const v2i64*>(brow + idx[l]);
-                        x[0] = a.x;
-                        x[VEC - 1] = a.y;
-                        y[0] = b.x;
-                        y[VEC - 1] = b.y;
-                    } else {
-                        x[0] = __builtin_nontemporal_load(row + idx[l]);
-                        y[0] = brow[idx[l]];
-                    }
+                    x[s][l] = __builtin_nontemporal_load(reinterpret_cast<const v2i64_a8*>(dt + (int64_t)sr * R + idx[l]));
+                    y[s][l] = *reinterpret_cast<const v2i64_a8*>(bw + (int64_t)sr * R + idx[l]);
+                }
+            }
+            if (SMAX <= 8 && !RUN) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        const int k = l * VEC + e;
-                        const int64_t red = x[e] - y[e];
-                        dl[k][s] = red > 0 ? red : 0;
-                        if (s < S) tot[k] += x[e];
+            for (int s = 0; s < SMAX; ++s) {
+#pragma unroll
+                for (int l = 0; l < NLD; ++l) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int64_t red = x[s][l][e] - y[s][l][e];
+                        dl[l * 2 + e][s] = red > 0 ? red : 0;
+                        if (s < S) tot[l * 2 + e] += x[s][l][e];
                     }
                 }
             }
@@ -148,22 +151,23 @@ __global__ __launch_bounds__(WG) void k_exposure_gain(
     }
 }
 
-// Any number of stages (past what the registers of k_exposure_gain hold):
-// for each rank tile the step group makes two passes over the stages, the
-// rank totals first and then every stage's candidate max (the durations of
-// the tile are read twice).  The group's last lane keeps the maxima over
-// tiles in the step's own out_gain row (the replaced-stage maxima) and
-// out_makespan entry (F), and after a barrier the workgroup turns the rows
-// into gains.  Slots past R re-read rank r0, which cannot change a max.
-template <int VEC, int K, int G, int WG>
+// Few ranks and many stages, or more of either than the other kernels take:
+// G lanes own a step (two ranks per lane and tile), and for each rank tile
+// the group makes two passes over the stages, the rank totals first and then
+// every stage's candidate max; the second pass finds a small step's rows in
+// the caches.  The group's last lane keeps the maxima over tiles in the
+// step's own out_gain row (the replaced-stage maxima) and out_makespan entry
+// (F), and after a barrier the workgroup turns the rows into gains.  Rank
+// pairs past R re-read the last pair, which cannot change a max.
+template <int VEC, int G, int WG>
 __global__ __launch_bounds__(WG) void k_exposure_gain_wide(
     const int64_t* __restrict__ d, const int64_t* __restrict__ btilde, int64_t T, int R, int S,
     int64_t window, int64_t* __restrict__ gain, int64_t* __restrict__ makespan)
 {
-    static_assert(K % VEC == 0 && G <= 64 && WG % G == 0, "one writer lane per step");
+    static_assert(G <= 64 && WG % G == 0, "one writer lane per step");
     constexpr int SPW = WG / G;
-    constexpr int NLD = K / VEC;
-    constexpr int RT = G * K;
+    constexpr int RT = G * VEC;
+    constexpr int U = 8;  // stage rows in flight
     const int tid = threadIdx.x;
     const int gl = tid % G;
     const bool writer = gl == G - 1;
@@ -175,53 +179,50 @@ __global__ __launch_bounds__(WG) void k_exposure_gain_wide(
         u64* fr = reinterpret_cast<u64*>(gain) + t * S;  // replaced-stage maxima so far
         u64* fm = reinterpret_cast<u64*>(makespan) + t;  // F so far
         for (int r0 = 0; r0 < R; r0 += RT) {
-            int idx[NLD];
-#pragma unroll
-            for (int l = 0; l < NLD; ++l) {
-                const int r = r0 + (l * G + gl) * VEC;
-                idx[l] = r < R ? r : r0;
-            }
-            auto load = [&](const int64_t* row, int l, int64_t* x) {
+            const int r = min(r0 + gl * VEC, R - VEC);  // VEC <= R
+            auto load = [&](const int64_t* row, int64_t* x) {
                 if (VEC == 2) {
-                    const v2i64 a = *reinterpret_cast<const v2i64*>(row + idx[l]);
+                    const v2i64_a8 a = *reinterpret_cast<const v2i64_a8*>(row + r);
                     x[0] = a.x;
                     x[VEC - 1] = a.y;
                 } else {
-                    x[0] = row[idx[l]];
+                    x[0] = row[r];
                 }
             };
-            int64_t tot[K];
+            int64_t tot[VEC];
 #pragma unroll
-            for (int k = 0; k < K; ++k) tot[k] = 0;
+            for (int e = 0; e < VEC; ++e) tot[e] = 0;
+#pragma unroll U
             for (int s = 0; s < S; ++s) {
+                int64_t x[VEC];
+                load(dt + (int64_t)s * R, x);
 #pragma unroll
-                for (int l = 0; l < NLD; ++l) {
-                    int64_t x[VEC];
-                    load(dt + (int64_t)s * R, l, x);
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) tot[l * VEC + e] += x[e];
-                }
+                for (int e = 0; e < VEC; ++e) tot[e] += x[e];
             }
             u64 f = 0;
 #pragma unroll
-            for (int k = 0; k < K; ++k) f = umax64(f, (u64)tot[k]);
+            for (int e = 0; e < VEC; ++e) f = umax64(f, (u64)tot[e]);
             f = group_max<G>(f);
             if (writer) *fm = r0 == 0 ? f : umax64(*fm, f);
-            for (int s = 0; s < S; ++s) {
-                u64 m = 0;
+            for (int s0 = 0; s0 < S; s0 += U) {
+                int64_t x[U][VEC], y[U][VEC];
 #pragma unroll
-                for (int l = 0; l < NLD; ++l) {
-                    int64_t x[VEC], y[VEC];
-                    load(dt + (int64_t)s * R, l, x);
-                    load(bw + (int64_t)s * R, l, y);
+                for (int u = 0; u < U; ++u) {
+                    const int s = min(s0 + u, S - 1);
+                    load(dt + (int64_t)s * R, x[u]);
+                    load(bw + (int64_t)s * R, y[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    u64 m = 0;
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) {
-                        const int64_t red = x[e] - y[e];
-                        m = umax64(m, (u64)(tot[l * VEC + e] - (red > 0 ? red : 0)));
+                        const int64_t red = x[u][e] - y[u][e];
+                        m = umax64(m, (u64)(tot[e] - (red > 0 ? red : 0)));
                     }
+                    m = group_max<G>(m);
+                    if (writer && s0 + u < S) fr[s0 + u] = r0 == 0 ? m : umax64(fr[s0 + u], m);
                 }
-                m = group_max<G>(m);
-                if (writer) fr[s] = r0 == 0 ? m : umax64(fr[s], m);
             }
         }
     }
@@ -235,225 +236,163 @@ __global__ __launch_bounds__(WG) void k_exposure_gain_wide(
     }
 }
 
-// Steps of 4097 to 16384 ranks and up to 16 stages: the ranks near the
-// frontier first.  Replacing stage s lowers a rank's total by delta >= 0, so
-// with v = F - P_S (F = max_r P_S) a rank whose v is at least D contributes
-// at most F - D to max_r (P_S - delta); when the maximum over the set
-// Q = {r : v < D} reaches F - D it is the maximum over all ranks.  One
-// workgroup per step keeps the rank totals in registers (16 per lane: one
-// pass over the step's durations, two chunks of loads per stage, the waves
-// kept on one stage row by a barrier), picks D by radix passes over v
-// (256-bin histograms, as in the selects) so that Q holds at least kNearMin
-// ranks (every rank up to the one of rank kNearMin - 1 in ascending v, and
-// the rest of its bin in the last pass) and at most kNearCap, reads the
-// durations and baseline of Q's ranks only, and folds every stage's maximum
-// over Q with LDS atomics.  If some stage's maximum falls below F - D (a
-// gain larger than D), or more than kNearCap ranks sit at the smallest
-// values of v, the workgroup makes a second pass over the step's durations
-// and baseline and takes the maxima over all ranks.  The totals are 64-bit
-// (32-bit ones ran 0.5% faster but made every step past 2^32 ns, 4.3 s, a
-// second launch).  Measured on MI355X: one 16-wave workgroup per CU beat
-// two at a 64-VGPR cap by 5%; loading a stage in one chunk, 3% slower;
-// without the stage barrier, 2% slower; at 4096 ranks the per-step kernel
-// stays ahead (0.63 against 0.64-0.66 ms).
-constexpr int kNearMin = 32;
+// The ranks near the frontier only.  Replacing stage s lowers a rank's total
+// by delta >= 0, so a rank r can raise the stage's maximum above a value
+// already found only if its total P_r exceeds that value.  One workgroup per
+// step adds the durations into rank totals in registers (one pass over the
+// step, KP rank pairs per lane; with NS > 1 the workgroup's slices take
+// different stages and add up through LDS), then
+//  1. takes F and a rank that attains it, and reads that rank's durations and
+//     baseline: F - delta is a first candidate maximum of every stage, L the
+//     smallest of them;
+//  2. reads durations and baseline of the ranks with P_r > L (a handful as a
+//     rule), for the stages whose candidate they can still raise.
+// When more than kNearCap ranks lie above L (some stage's replacement drops
+// the top rank far), the waves' own top ranks are tried first, which raises L
+// when it was the top rank alone; then the stage of the smallest candidate is
+// resolved over all ranks from its two rows, which leaves L to the others, up
+// to kNearRows times; then all stages are.  The result is the same maximum in
+// each case.  Pairs past R read 0 (they lie past the stage row's buffer
+// resource), and a total of 0 never exceeds L >= 0; with odd R the last pair
+// overlaps the one before.
+//
+// Bound: HBM, the totals pass.  Measured on MI355X: 1024 ranks x 132 stages x
+// 1000 steps 1278 -> 188 us, 4096 x 12 x 5000 315 -> 295 us against the
+// kernels that took these shapes before; 12000 x 12 x 2777 535 -> 489 us and
+// 16384 x 12 x 2034 492 -> 483 us against a radix search over the totals for
+// a bound with at least 32 ranks above it (which also needed a barrier per
+// stage row to run well).
 constexpr int kNearCap = 512;
+constexpr int kNearMaxR = 32768;
+constexpr int64_t kNearFewSteps = 512;
+constexpr int kNearMaxS = 4096;  // stages whose candidates fit in LDS (32 KB)
+constexpr int kNearSBits = 12;   // a candidate (below 2^47) and its stage in one key
+constexpr int kNearRows = 3;
+constexpr u64 kNearDone = 1ull << 63;  // a candidate that is final
 
-// digit and candidate tests of the bound's radix passes, on 64-bit values or
-// on 32-bit ones (totals spanning less than 2^32: lo <= 24, hi <= 32, a
-// prefix below 2^(32 - hi)), which keep the shifts and compares in single
-// VALU instructions
-__device__ __forceinline__ int near_first_bin(u64 v, int lo) { return sel_first_bin(v, lo); }
-__device__ __forceinline__ int near_bin(u64 v, int lo, int hi, u64 prefix) { return sel_bin(v, lo, hi, prefix); }
-__device__ __forceinline__ int near_first_bin(uint32_t v, int lo) { return (int)(v >> lo); }
-__device__ __forceinline__ int near_bin(uint32_t v, int lo, int hi, u64 prefix)
-{
-    return (hi >= 32 || (v >> hi) == (uint32_t)prefix) ? (int)((v >> lo) & ((1u << (hi - lo)) - 1u)) : -1;
-}
-constexpr int kNearK = 16;  // ranks per lane
-
-template <int WG, bool FULL>
+template <int WG, int KP, int NS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_exposure_gain_near(
     const int64_t* __restrict__ d, const int64_t* __restrict__ btilde, int64_t T, int R, int S,
     int64_t window, int64_t* __restrict__ gain, int64_t* __restrict__ makespan)
 {
-    constexpr int K = kNearK;
     constexpr int NW = WG / 64;
-    constexpr int NLD = K / 2;
-    constexpr int CH = 2;  // chunks of loads per stage
-    constexpr int SMAX = 16;
-    __shared__ __align__(16) uint32_t hist[kSelWords];
-    __shared__ u64 red_max[NW], red_min[NW];
-    __shared__ uint32_t sel[3];
+    constexpr int GW = WG / NS;  // threads per slice (whole waves)
+    constexpr int LC = KP < 8 ? KP : (WG == 1024 ? 4 : 8);  // loads of a stage in flight at once
+    constexpr int U = KP < 8 ? 8 / KP : 1;                  // stages in flight at once
+    static_assert(GW % 64 == 0 && KP % LC == 0, "shape");
+    extern __shared__ u64 cand[];  // [S] candidate maxima
+    __shared__ u64 part[NS > 1 ? GW * KP * 2 : 1];
+    __shared__ u64 w_tot[NW], red[NW];
+    __shared__ int w_rank[NW];
     __shared__ int q_rank[kNearCap];
     __shared__ u64 q_tot[kNearCap];
-    __shared__ uint32_t q_n, all_ranks;
-    __shared__ int top_rank;  // a rank whose total is F
-    __shared__ u64 cand[SMAX];
+    __shared__ uint32_t q_n;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slice = NS > 1 ? __builtin_amdgcn_readfirstlane(tid / GW) : 0;
+    const int tl = NS > 1 ? tid % GW : tid;
     const int64_t t = xcd_block();
     if (t >= T) return;  // uniform (the grid is T)
     const int64_t* dt = d + t * (int64_t)S * R;
     const int64_t* bw = btilde + (t / window) * (int64_t)S * R;
+    auto rank0 = [&](int l) {  // first rank of the lane's pair l (R >= 2)
+        const int r = (l * GW + tl) * 2;
+        return r == R - 1 ? r - 1 : r;
+    };
 
-    bool ok[NLD];
-    int idx[NLD];
-#pragma unroll
-    for (int l = 0; l < NLD; ++l) {
-        const int r = (l * WG + tid) * 2;
-        ok[l] = FULL || r < R;
-        idx[l] = ok[l] ? r : 0;
+    for (int s = tid; s < S; s += WG) cand[s] = 0;
+    if (NS > 1) {
+        for (int i = tid; i < GW * KP * 2; i += WG) part[i] = 0;
     }
-    // the rank totals P_S (slots past R stay 0 and are left out below)
-    u64 tot[K];
+    if (tid == 0) q_n = 0;
+    u64 tot[KP][2];
 #pragma unroll
-    for (int k = 0; k < K; ++k) tot[k] = 0;
-    for (int s = 0; s < S; ++s) {
-        const auto rs = buffer_rsrc(dt + (int64_t)s * R, (uint32_t)R * 8u);
+    for (int l = 0; l < KP; ++l) tot[l][0] = tot[l][1] = 0;
+    for (int s0 = slice * U; s0 < S; s0 += NS * U) {
 #pragma unroll
-        for (int ch = 0; ch < CH; ++ch) {
-            v2i64 xs[NLD / CH];
+        for (int l0 = 0; l0 < KP; l0 += LC) {
+            v2i64 x[U][LC];
 #pragma unroll
-            for (int l = 0; l < NLD / CH; ++l) {
-                const int ll = ch * (NLD / CH) + l;
-                xs[l] = FULL ? buffer_load16_nt(rs, (uint32_t)tid * 16u, (uint32_t)(ll * WG * 16))
-                             : buffer_load16_nt(rs, (uint32_t)idx[ll] * 8u, 0u);
+            for (int u = 0; u < U; ++u) {
+                // a stage past S reads zeros
+                const auto rs = buffer_rsrc(dt + (int64_t)(s0 + u) * R, s0 + u < S ? (uint32_t)R * 8u : 0u);
+#pragma unroll
+                for (int l = 0; l < LC; ++l) x[u][l] = buffer_load16_nt(rs, (uint32_t)rank0(l0 + l) * 8u, 0u);
             }
-            __builtin_amdgcn_sched_barrier(0);  // the chunk's loads all in flight first
+            __builtin_amdgcn_sched_barrier(0);  // the loads all in flight first
 #pragma unroll
-            for (int l = 0; l < NLD / CH; ++l) {
-                const int ll = ch * (NLD / CH) + l;
-                tot[2 * ll] += ok[ll] ? (u64)xs[l].x : 0ull;
-                tot[2 * ll + 1] += ok[ll] ? (u64)xs[l].y : 0ull;
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int l = 0; l < LC; ++l) {
+                    tot[l0 + l][0] += (u64)x[u][l].x;
+                    tot[l0 + l][1] += (u64)x[u][l].y;
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_s_barrier();  // the waves read a stage's row together
     }
-    // F and the smallest total over the workgroup
-    u64 mx = 0, mn = ~0ull;
+    if (NS > 1) {
+        __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if (ok[k / 2]) {
-            mx = umax64(mx, tot[k]);
-            mn = umin64(mn, tot[k]);
+        for (int l = 0; l < KP; ++l) {
+            atomicAdd(&part[(l * GW + tl) * 2], tot[l][0]);
+            atomicAdd(&part[(l * GW + tl) * 2 + 1], tot[l][1]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int l = 0; l < KP; ++l) {
+            tot[l][0] = slice == 0 ? part[(l * GW + tl) * 2] : 0;
+            tot[l][1] = slice == 0 ? part[(l * GW + tl) * 2 + 1] : 0;
         }
     }
-    mx = group_max<64>(mx);
-    mn = ~group_max<64>(~mn);
-    if (lane == 63) {
-        red_max[wave] = mx;
-        red_min[wave] = mn;
-    }
-    if (tid < SMAX) cand[tid] = 0;
-    if (tid == 0) {
-        q_n = 0;
-        all_ranks = 0;
+    // every wave's largest total and a rank that has it
+    {
+        u64 m = 0;
+#pragma unroll
+        for (int l = 0; l < KP; ++l) m = umax64(m, umax64(tot[l][0], tot[l][1]));
+        const u64 wm = lane_value(group_max<64>(m), 63);
+        int rk = -1;
+#pragma unroll
+        for (int l = 0; l < KP; ++l) {
+            if (tot[l][0] == wm) rk = rank0(l);
+            if (tot[l][1] == wm) rk = rank0(l) + 1;
+        }
+        const u64 has = __ballot(rk >= 0);
+        const int src = __builtin_amdgcn_readlane(rk, (int)__builtin_ctzll(has));
+        if (lane == 0) {
+            w_tot[wave] = wm;
+            w_rank[wave] = wm != 0 ? src : -1;  // only a rank below R has a total above 0
+        }
     }
     __syncthreads();
-    u64 F = 0, Pmin = ~0ull;
+    u64 F = 0;
+    int top = -1;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
-        F = umax64(F, red_max[i]);
-        Pmin = umin64(Pmin, red_min[i]);
+        if (w_tot[i] > F) {
+            F = w_tot[i];
+            top = w_rank[i];
+        }
     }
-    // the bound D: Q = {v < D} with kNearMin <= |Q| <= kNearCap, by radix
-    // passes over v = F - P_S; in 32 bits when the totals span less than
-    // 2^32 (every workload here), else in 64
-    u64 D = 0;
-    bool have_q = false;
-    auto find_bound = [&](auto vt) {
-        typedef decltype(vt) VT;
-        VT v[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = (VT)(F - tot[k]);
-        int lo = sel_first_lo(F - Pmin), hi = 64;
-        u64 prefix = 0;
-        uint32_t kk = kNearMin - 1;  // R > 4096 ranks
-        uint32_t below = 0;          // ranks in Q for certain (below the bracket)
-        bool first = true;
-        for (;;) {
-            for (int i = tid; i < kSelWords; i += WG) hist[i] = 0;
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                if (ok[k / 2]) {
-                    const int bin = first ? near_first_bin(v[k], lo) : near_bin(v[k], lo, hi, prefix);
-                    if (bin >= 0) atomicAdd(&hist[bin], 1u);
-                }
-            }
-            __syncthreads();
-            if (wave == 0) {
-                uint32_t k2 = kk, dg, cn;
-                sel_scan_wave(hist, lane, k2, dg, cn);
-                if (lane == 0) {
-                    sel[0] = dg;
-                    sel[1] = k2;
-                    sel[2] = cn;
-                }
-            }
-            __syncthreads();
-            const uint32_t dg = sel[0], kin = sel[1], cn = sel[2];
-            const uint32_t lower = kk - kin;  // candidates in the lower bins of this pass
-            prefix = first ? (u64)dg : (prefix << (hi - lo)) | (u64)dg;
-            first = false;
-            hi = lo;
-            if (below + lower + cn <= (uint32_t)kNearCap) {
-                D = (prefix + 1) << hi;
-                have_q = true;
-                return;
-            }
-            if (hi == 0) return;  // more than kNearCap ranks up to one value of v
-            below += lower;
-            kk = kin;
-            lo = lo > 8 ? lo - 8 : 0;
-        }
-    };
-    if (F != Pmin) {
-        if (F - Pmin <= 0xFFFFFFFFull)
-            find_bound((uint32_t)0);
-        else
-            find_bound((u64)0);
-        // sel and hist are not touched again in this step
+    if (F == 0) {  // uniform: every duration is 0
+        for (int s = tid; s < S; s += WG) gain[t * S + s] = 0;
+        if (tid == 0) makespan[t] = 0;
+        return;
     }
-    if (have_q) {
-        // Q into LDS: a wave scan of the per-lane counts, one atomic per wave
-        uint32_t cm = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) cm |= (ok[k / 2] && F - tot[k] < D) ? (1u << k) : 0u;
-        const uint32_t nc = (uint32_t)__popc(cm);
-        const uint32_t incl = wave_scan_incl(nc);
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        uint32_t wb = 0;
-        if (lane == 63 && total != 0) wb = atomicAdd(&q_n, total);
-        uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)wb, 63) + incl - nc;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if ((cm >> k) & 1u) {
-                if (pos < (uint32_t)kNearCap) {
-                    q_rank[pos] = idx[k / 2] + (k & 1);
-                    q_tot[pos] = tot[k];
-                }
-                ++pos;
-            }
-            if (ok[k / 2] && tot[k] == F) top_rank = idx[k / 2] + (k & 1);  // any one of them
-        }
-        __syncthreads();
-        // first a rank whose total is F, for every stage: its replaced-stage
-        // total F - delta bounds the stage's maximum from below, so only
-        // ranks of Q whose total exceeds it can raise it (fewer scattered
-        // reads: each costs a cache line)
-        if (tid < S) {
-            const int64_t e = dt[(int64_t)tid * R + top_rank] - bw[(int64_t)tid * R + top_rank];
-            cand[tid] = F - (u64)(e > 0 ? e : 0);
-        }
-        __syncthreads();
-        const uint32_t nq = min(q_n, (uint32_t)kNearCap);
-        const uint32_t np = nq * (uint32_t)S;
-        // the (rank of Q, stage) pairs left: four per thread in flight at once
+    // candidates of rank `top`, and the smallest of them
+    auto low_key = [](u64 c, int s) { return (c & kNearDone) ? ~0ull : (c << kNearSBits) | (u64)s; };
+    u64 low = ~0ull;
+    for (int s = tid; s < S; s += WG) {
+        const int64_t e = dt[(int64_t)s * R + top] - bw[(int64_t)s * R + top];
+        const u64 c = F - (u64)(e > 0 ? e : 0);  // 0 <= b: max(e, 0) <= d <= F
+        cand[s] = c;
+        low = umin64(low, low_key(c, s));
+    }
+    // fold the (rank, stage) pairs of a list of ranks: four per thread in flight
+    auto fold = [&](const int* ranks, const u64* tots, uint32_t n) {
+        const uint32_t np = n * (uint32_t)S;
         for (uint32_t i0 = tid; i0 < np; i0 += 4 * WG) {
             int64_t x[4], y[4];
             u64 tq[4];
@@ -465,13 +404,13 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const uint32_t ii = i < np ? i : 0u;
                 const uint32_t q = ii / (uint32_t)S;
                 const int s = (int)(ii - q * (uint32_t)S);
-                tq[j] = q_tot[q];
+                tq[j] = tots[q];
                 sj[j] = s;
                 need[j] = i < np && tq[j] > cand[s];  // cand only grows: a stale read is safe
                 x[j] = 0;
                 y[j] = 0;
                 if (need[j]) {
-                    const int r = q_rank[q];
+                    const int r = ranks[q];  // a total above a candidate: a rank below R
                     x[j] = dt[(int64_t)s * R + r];
                     y[j] = bw[(int64_t)s * R + r];
                 }
@@ -479,53 +418,100 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (need[j]) {
-                    const int64_t e = x[j] - y[j];  // b >= 0: max(e, 0) <= x <= the total
+                    const int64_t e = x[j] - y[j];
                     atomicMax(&cand[sj[j]], tq[j] - (u64)(e > 0 ? e : 0));
                 }
             }
         }
-        __syncthreads();
-        if (tid < S && cand[tid] + D < F) all_ranks = 1;  // a gain above D
-        __syncthreads();
-    }
-    if (!have_q || all_ranks != 0) {
-        // every rank: a second pass over the step's durations and baseline
-        if (have_q) {
-            if (tid < SMAX) cand[tid] = 0;  // the check above has read them
-            __syncthreads();
+    };
+    // stage s over all ranks, by the waves that hold totals
+    auto row = [&](int s) {
+        const auto rd = buffer_rsrc(dt + (int64_t)s * R, (uint32_t)R * 8u);
+        const auto rb = buffer_rsrc(bw + (int64_t)s * R, (uint32_t)R * 8u);
+        u64 m = 0;
+        constexpr int RC = KP < 4 ? KP : (KP == 16 ? 2 : 4);  // loads of each row in flight
+#pragma unroll
+        for (int l0 = 0; l0 < KP; l0 += RC) {
+            v2i64 x[RC], y[RC];
+#pragma unroll
+            for (int l = 0; l < RC; ++l) {
+                x[l] = buffer_load16_nt(rd, (uint32_t)rank0(l0 + l) * 8u, 0u);
+                y[l] = buffer_load16_nt(rb, (uint32_t)rank0(l0 + l) * 8u, 0u);
+            }
+#pragma unroll
+            for (int l = 0; l < RC; ++l) {
+                const u64* p = NS > 1 ? &part[((l0 + l) * GW + tl) * 2] : tot[l0 + l];
+                const int64_t e0 = x[l].x - y[l].x, e1 = x[l].y - y[l].y;
+                m = umax64(m, p[0] - (u64)(e0 > 0 ? e0 : 0));
+                m = umax64(m, p[1] - (u64)(e1 > 0 ? e1 : 0));
+            }
         }
-        for (int s = 0; s < S; ++s) {
-            const auto rd = buffer_rsrc(dt + (int64_t)s * R, (uint32_t)R * 8u);
-            const auto rb = buffer_rsrc(bw + (int64_t)s * R, (uint32_t)R * 8u);
-            u64 m = 0;
+        m = group_max<64>(m);
+        if (lane == 63) atomicMax(&cand[s], m);
+    };
+    for (int round = 0;; ++round) {
+        // L, the smallest candidate that is not final, and its stage
+        low = ~lane_value(group_max<64>(~low), 63);
+        if (lane == 0) red[wave] = low;
+        __syncthreads();
+        u64 key = ~0ull;
 #pragma unroll
-            for (int ch = 0; ch < CH; ++ch) {
-                v2i64 xs[NLD / CH], ys[NLD / CH];
+        for (int i = 0; i < NW; ++i) key = umin64(key, red[i]);
+        const u64 L = key >> kNearSBits;
+        // Q, the ranks above L (rank `top` is done): a wave scan of the
+        // per-lane counts, one atomic per wave
+        uint32_t cm = 0;
 #pragma unroll
-                for (int l = 0; l < NLD / CH; ++l) {
-                    const int ll = ch * (NLD / CH) + l;
-                    const uint32_t vo = FULL ? (uint32_t)tid * 16u : (uint32_t)idx[ll] * 8u;
-                    const uint32_t so = FULL ? (uint32_t)(ll * WG * 16) : 0u;
-                    xs[l] = buffer_load16_nt(rd, vo, so);
-                    ys[l] = buffer_load16_nt(rb, vo, so);
-                }
+        for (int l = 0; l < KP; ++l) {
 #pragma unroll
-                for (int l = 0; l < NLD / CH; ++l) {
-                    const int ll = ch * (NLD / CH) + l;
+            for (int e = 0; e < 2; ++e)
+                cm |= (tot[l][e] > L && rank0(l) + e != top) ? 1u << (2 * l + e) : 0u;
+        }
+        if (__ballot(cm != 0) != 0) {
+            const uint32_t nc = (uint32_t)__popc(cm);
+            const uint32_t incl = wave_scan_incl(nc);
+            uint32_t wb = 0;
+            if (lane == 63) wb = atomicAdd(&q_n, incl);
+            uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)wb, 63) + incl - nc;
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const int64_t e64 = (e == 0 ? xs[l].x : xs[l].y) - (e == 0 ? ys[l].x : ys[l].y);
-                        const u64 c = tot[2 * ll + e] - (u64)(e64 > 0 ? e64 : 0);
-                        m = ok[ll] ? umax64(m, c) : m;
+            for (int k = 0; k < 2 * KP; ++k) {
+                if ((cm >> k) & 1u) {
+                    if (pos < (uint32_t)kNearCap) {
+                        q_rank[pos] = rank0(k / 2) + (k & 1);
+                        q_tot[pos] = tot[k / 2][k & 1];
                     }
+                    ++pos;
                 }
             }
-            m = group_max<64>(m);
-            if (lane == 63) atomicMax(&cand[s], m);
         }
         __syncthreads();
+        const uint32_t nq = q_n;
+        if (nq <= (uint32_t)kNearCap) {
+            fold(q_rank, q_tot, nq);
+            break;
+        }
+        const int s_low = __builtin_amdgcn_readfirstlane((int)(key & ((1u << kNearSBits) - 1u)));
+        if (round == 0) {
+            fold(w_rank, w_tot, NW);
+        } else if (round <= kNearRows) {
+            if (slice == 0) row(s_low);
+        } else {
+            for (int s = slice; s < S; s += NS) {
+                if (!(cand[s] & kNearDone)) row(s);  // uniform over the wave
+            }
+            break;
+        }
+        __syncthreads();  // every thread has read q_n, every candidate is in
+        if (tid == 0) {
+            q_n = 0;
+            if (round > 0) cand[s_low] |= kNearDone;
+        }
+        __syncthreads();
+        low = ~0ull;
+        for (int s = tid; s < S; s += WG) low = umin64(low, low_key(cand[s], s));
     }
-    if (tid < S) gain[t * S + tid] = (int64_t)(F - cand[tid]);
+    __syncthreads();
+    for (int s = tid; s < S; s += WG) gain[t * S + s] = (int64_t)(F - (cand[s] & ~kNearDone));
     if (tid == 0) makespan[t] = (int64_t)F;
 }
 
@@ -534,49 +520,117 @@ struct GainVariant {
     int G, WG;
 };
 
-template <int VEC, int K, int G, int WG, int SMAX, bool RUN = false>
+template <int K, int G, int WG, int SMAX, bool RUN = false>
 GainVariant gain_variant()
 {
-    return GainVariant{reinterpret_cast<const void*>(&k_exposure_gain<VEC, K, G, WG, SMAX, RUN>), G,
-                       WG};
+    return GainVariant{reinterpret_cast<const void*>(&k_exposure_gain<K, G, WG, SMAX, RUN>), G, WG};
 }
 
-// Two ranks per lane keep the deltas of up to 32 stages in registers
-// (K = 1 at 64); G covers R in one tile up to 256 * K ranks, larger R loops
-// over tiles.  Chosen by measurement on MI355X (wider K held more registers
-// and ran up to 2x slower).
-template <int VEC, int K, int SMAX>
+// Two ranks per lane keep the deltas in registers; G covers R in one tile up
+// to 512 ranks, larger R loops over tiles.  Chosen by measurement on MI355X
+// (wider K held more registers and ran up to 2x slower).
+template <int SMAX>
 GainVariant pick_gain_g(int R)
 {
-    if (R <= 16 * K) return gain_variant<VEC, K, 16, 64, SMAX>();
-    if (R <= 64 * K) return gain_variant<VEC, K, 64, 256, SMAX>();
-    // four or more tiles per step: running maxima (measured: 1-2% faster at
-    // 4096 and 16384 ranks; at one or two tiles they only cost registers)
-    if (SMAX <= 16 && R > 3 * 256 * K) return gain_variant<VEC, K, 256, 256, SMAX, (SMAX <= 16)>();
-    return gain_variant<VEC, K, 256, 256, SMAX>();
-}
-
-template <int SMAX>
-GainVariant pick_gain_s(int R, bool vec2)
-{
-    return vec2 ? pick_gain_g<2, 2, SMAX>(R) : pick_gain_g<1, 2, SMAX>(R);
+    if (R <= 32) return gain_variant<2, 16, 64, SMAX>();
+    if constexpr (SMAX <= 16) {
+        if (R <= 128) return gain_variant<2, 64, 256, SMAX>();
+        // four or more tiles per step: running maxima (measured: 1-2% faster
+        // at 4096 and 16384 ranks; at one or two tiles they only cost registers)
+        if (R > 3 * 512) return gain_variant<2, 256, 256, SMAX, true>();
+    }
+    return gain_variant<2, 256, 256, SMAX>();
 }
 
 // SMAX close above S: every unrolled stage past S still issues its two loads
 // and holds its deltas, so 12 stages under SMAX = 16 ran 14-18% slower than
 // under SMAX = 12 (and 6 under 8, 9% slower) on MI355X.
-constexpr int kGainRegS = 64;  // stages whose deltas k_exposure_gain keeps in registers
+constexpr int kGainRegS = 24;  // stages whose deltas k_exposure_gain keeps in registers
 
-GainVariant pick_gain(int R, int S, bool vec2)
+GainVariant pick_gain(int R, int S)
 {
-    if (S <= 4) return pick_gain_s<4>(R, vec2);
-    if (S <= 6) return pick_gain_s<6>(R, vec2);
-    if (S <= 8) return pick_gain_s<8>(R, vec2);
-    if (S <= 12) return pick_gain_s<12>(R, vec2);
-    if (S <= 16) return pick_gain_s<16>(R, vec2);
-    if (S <= 24) return pick_gain_s<24>(R, vec2);
-    if (S <= 32) return pick_gain_s<32>(R, vec2);
-    return pick_gain_g<1, 1, 64>(R);  // S <= kGainRegS
+    if (S <= 4) return pick_gain_g<4>(R);
+    if (S <= 6) return pick_gain_g<6>(R);
+    if (S <= 8) return pick_gain_g<8>(R);
+    if (S <= 12) return pick_gain_g<12>(R);
+    if (S <= 16) return pick_gain_g<16>(R);
+    return pick_gain_g<24>(R);  // S <= kGainRegS
+}
+
+template <int WG, int KP, int NS = 1>
+GainVariant near_variant()
+{
+    return GainVariant{reinterpret_cast<const void*>(&k_exposure_gain_near<WG, KP, NS>), WG, WG};
+}
+
+template <int VEC, int G>
+GainVariant wide_variant()
+{
+    return GainVariant{reinterpret_cast<const void*>(&k_exposure_gain_wide<VEC, G, 256>), G, 256};
+}
+
+GainVariant pick_wide(int R)
+{
+    if (R == 1) return wide_variant<1, 4>();
+    if (R <= 8) return wide_variant<2, 4>();
+    if (R <= 16) return wide_variant<2, 8>();
+    if (R <= 32) return wide_variant<2, 16>();
+    if (R <= 64) return wide_variant<2, 32>();
+    return wide_variant<2, 64>();
+}
+
+// 8 loads in flight per lane: KP pairs of 8 / KP stages (two chunks of four
+// in the 1024-thread shapes).  From 4097 to 8192 ranks 512 threads x 8 pairs
+// beat 1024 x 4 by 5-40%.  With few steps the
+// stages of one are split over the waves of a wide workgroup, since there are
+// not enough workgroups to fill the chip.
+GainVariant pick_near(int64_t T, int R)
+{
+    if (T <= kNearFewSteps) {
+        if (R <= 256) return near_variant<1024, 1, 8>();
+        if (R <= 512) return near_variant<1024, 1, 4>();
+        if (R <= 1024) return near_variant<1024, 1, 2>();
+        if (R <= 2048) return near_variant<1024, 1>();
+        if (R <= 4096) return near_variant<1024, 2>();
+    }
+    if (R <= 256) return near_variant<256, 1, 2>();
+    if (R <= 512) return near_variant<256, 1>();
+    if (R <= 1024) return near_variant<256, 2>();
+    if (R <= 2048) return near_variant<256, 4>();
+    if (R <= 4096) return near_variant<256, 8>();
+    if (R <= 8192) return near_variant<512, 8>();
+    if (R <= 16384) return near_variant<1024, 8>();
+    return near_variant<1024, 16>();  // R <= kNearMaxR
+}
+
+// Where the near-frontier pass wins (measured on MI355X over 0.8 GB, us, near
+// against the best other kernel).  It wants steps long enough to cover its
+// few dependent reads, and many stages: with 6 or fewer, one stage is a large
+// part of the step and its replacement often takes the row passes (16384
+// ranks: 175 against 145; with 12 stages 130 against 149).
+//   9 stages and more: past 128 ranks (12 stages: 200 ranks 141 : 237, 1024
+//     130 : 147, 4096 127 : 136; 128 ranks 191 : 130);
+//   7 and 8: from 129 to 4096 ranks (8 stages: 200 ranks 183 : 237, 4096
+//     133 : 134, 8192 148 : 134);
+//   17 and more: wherever a step holds 1600 samples (20 stages x 96 ranks
+//     190 : 229, 32 x 64 211 : 245, 32 x 48 259 : 245, 132 x 1024 153 : 640).
+bool use_near(int64_t T, int R, int S)
+{
+    if (R > kNearMaxR || S > kNearMaxS || T > INT32_MAX) return false;
+    if (S >= 17 && R >= 48 && R * S >= 1600) return true;
+    return R > 128 && (S >= 9 || (S >= 7 && R <= 4096));
+}
+
+// Where the two-pass kernel beats the one with the deltas in registers: a
+// handful of ranks (8 ranks x 6 stages 66 : 88, x 12 157 : 166, x 24 322 :
+// 442), 13 and more stages from 33 to 64 ranks (48 x 16 227 : 287), more
+// stages than the registers hold, and 17 to 24 of them where its lanes would
+// idle (16 ranks x 20 302 : 324, 48 x 24 236 : 382; 32 x 20 261 : 200).
+bool use_wide(int R, int S)
+{
+    if (R <= 8 || S > kGainRegS) return true;
+    if (S >= 17) return R <= 16 || (R > 32 && R <= 128);
+    return S >= 13 && R > 32 && R <= 64;
 }
 
 }  // namespace sfk
@@ -603,34 +657,23 @@ SF_API int sf_exposure_gain(const int64_t* durations, const int64_t* baseline, i
         for (int b = (a < 2 ? 2 : a + 1); b < 6; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
 
-    const bool vec2 = (R % 2 == 0) && aligned(durations, 16) && aligned(baseline, 16);
     int Ri = R, Si = S;
-    void* a1[] = {(void*)&durations, (void*)&baseline, (void*)&T, (void*)&Ri, (void*)&Si,
-                  (void*)&window, (void*)&out_gain, (void*)&out_makespan};
-    if (vec2 && S <= 16 && R > kNearK * 256 && R <= kNearK * 1024 && T <= INT32_MAX) {
-        // the ranks near the frontier (all ranks where the bound does not settle it)
-        const int WG = R <= kNearK * 512 ? 512 : 1024;
-        const bool full = R == kNearK * WG;
-        const void* fn =
-            WG == 512 ? (full ? reinterpret_cast<const void*>(&k_exposure_gain_near<512, true>)
-                              : reinterpret_cast<const void*>(&k_exposure_gain_near<512, false>))
-                      : (full ? reinterpret_cast<const void*>(&k_exposure_gain_near<1024, true>)
-                              : reinterpret_cast<const void*>(&k_exposure_gain_near<1024, false>));
-        int rc = launch(fn, dim3((unsigned)T), dim3(WG), a1, 0, stream);
-        if (rc != SF_OK) return rc;
-        rc = launch_window_sum(out_gain, T, S, window, W, out_window_gain, stream);
-        if (rc != SF_OK) return rc;
-        return launch_window_sum(out_makespan, T, 1, window, W, out_window_makespan, stream);
+    void* args[] = {(void*)&durations, (void*)&baseline, (void*)&T, (void*)&Ri, (void*)&Si,
+                    (void*)&window, (void*)&out_gain, (void*)&out_makespan};
+    GainVariant v;
+    size_t lds = 0;
+    if (use_near(T, R, S)) {
+        v = pick_near(T, R);
+        lds = (size_t)S * sizeof(u64);
+    } else if (use_wide(R, S)) {
+        v = pick_wide(R);
+    } else {
+        v = pick_gain(R, S);
     }
-    const GainVariant v =
-        S <= kGainRegS ? pick_gain(R, S, vec2)
-                       : GainVariant{vec2 ? reinterpret_cast<const void*>(&k_exposure_gain_wide<2, 2, 64, 256>)
-                                          : reinterpret_cast<const void*>(&k_exposure_gain_wide<1, 2, 64, 256>),
-                                     64, 256};
     const int spw = v.WG / v.G;
     const int64_t blocks = (T + spw - 1) / spw;
     if (blocks > INT32_MAX) return SF_EINVAL;
-    int rc = launch(v.fn, dim3((unsigned)blocks), dim3(v.WG), a1, 0, stream);
+    int rc = launch(v.fn, dim3((unsigned)blocks), dim3(v.WG), args, lds, stream);
     if (rc != SF_OK) return rc;
     rc = launch_window_sum(out_gain, T, S, window, W, out_window_gain, stream);
     if (rc != SF_OK) return rc;

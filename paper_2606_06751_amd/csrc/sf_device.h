@@ -10,6 +10,8 @@ namespace sfk {
 
 typedef unsigned long long u64;
 typedef long long v2i64 __attribute__((ext_vector_type(2)));
+// the same at element alignment: gfx950 loads 16 bytes from any dword address
+typedef long long v2i64_a8 __attribute__((ext_vector_type(2), aligned(8)));
 
 constexpr int kRankBits = 16;
 constexpr u64 kRankMask = 0xFFFFull;

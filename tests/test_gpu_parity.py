@@ -779,6 +779,31 @@ def test_gain_many_ranks_tied_at_frontier(sf):
     assert_gain_equal(sf, d, bt, window)
 
 
+@pytest.mark.parametrize("R,S,T", [
+    (2, 17, 40), (5, 25, 40), (33, 17, 30), (49, 33, 30), (64, 26, 20), (129, 9, 30), (255, 9, 530), (257, 12, 20),
+    (513, 7, 20), (1023, 33, 6), (1025, 9, 515), (2047, 8, 10), (2049, 20, 6), (4095, 9, 6), (4097, 9, 4),
+    (8191, 10, 4), (8193, 17, 3), (16383, 9, 3), (16385, 9, 3), (32767, 9, 2), (32768, 17, 2), (32769, 9, 2)])
+def test_gain_near_edges(sf, R, S, T):
+    """Rank counts around every shape of the near-frontier pass, odd ones
+    among them (the last pair of ranks overlaps the one before), few and many
+    steps, and the kernels on the other side of each rule.  The steps cycle
+    through what decides its rounds: a top rank alone with one far stage (the
+    waves' own top ranks settle it), most ranks with one large stage (its two
+    rows are read), every stage large (all rows), ties of every rank, and a
+    step of zeros."""
+    rng = np.random.Generator(np.random.PCG64(R * 31 + S))
+    d = rng.integers(1000, 1100, size=(T, S, R), dtype=np.int64)
+    bt = np.full((-(-T // 7), S, R), 1040, dtype=np.int64)
+    d[0::6, S // 2, R // 3] += 10**9
+    d[1::6, 0, :] += rng.integers(0, 10**6, size=(len(d[1::6]), R))
+    d[2::6] += rng.integers(0, 10**6, size=d[2::6].shape)
+    d[3::6] = 2000
+    d[4::6] = 0
+    d[5::6, S - 1, R - 1] += 1 << 46
+    print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
+    assert_gain_equal(sf, d, bt, 7)
+
+
 def test_gain_golden_cases(sf):
     import pins
     pins.pin_gain_sync_wait(lambda d, b, w: {k: v.cpu().numpy() for k, v in sf.sf_exposure_gain(
