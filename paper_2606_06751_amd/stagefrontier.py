@@ -107,7 +107,14 @@ def _stream(stream, device):
     return torch.cuda.ExternalStream(int(stream), device=device)
 
 
+# the handle of a device's current stream without building a Stream object
+# (0.1 us against 2.1 per call)
+_current_handle = torch._C._cuda_getCurrentRawStream
+
+
 def _stream_handle(stream, device) -> int:
+    if stream is None:
+        return _current_handle(device.index)
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(_stream(stream, device).cuda_stream)
@@ -117,7 +124,12 @@ def _new(shape, dtype, device, stream, zero: bool = False) -> torch.Tensor:
     """An output the binding allocates for a call on ``stream``.  It is
     allocated (and, with ``zero``, cleared) on that stream, so the clear is
     ordered before the call's kernels and the caching allocator does not hand
-    the block to other work while they may still use it."""
+    the block to other work while they may still use it.  Without a stream
+    that is the device's current one, where torch allocates anyway: entering
+    a stream context cost 10 us per output, 95 -> 35 us for a small
+    ``sf_frontier`` + ``sf_window_summary`` + ``sf_route``."""
+    if stream is None:
+        return (torch.zeros if zero else torch.empty)(shape, dtype=dtype, device=device)
     with torch.cuda.stream(_stream(stream, device)):
         if zero:
             return torch.zeros(shape, dtype=dtype, device=device)
