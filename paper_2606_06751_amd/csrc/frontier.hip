@@ -18,7 +18,13 @@
 // smaller) sub-group stores the partial max in LDS.  After the last stage
 // the workgroup decodes F and the leader per (step, stage), takes the
 // advance F[s] - F[s-1] and writes [T][S] rows with contiguous stores.
-// Durations are read exactly once, with 16-byte loads when R is even.
+// Durations are read exactly once, in 16-byte loads of rank pairs at any
+// 8-byte alignment (odd R shifts every other row by half a load).
+//
+// The large shapes keep one stage row per lane group in flight and rely on
+// many steps at once to fill the memory system.  With few steps the pass is
+// bound by latency instead: the deep shapes spread a step over more lanes
+// (2 to 16 ranks each) and keep D stage rows in flight.
 //
 // Stage counts beyond what LDS holds (the gradient-accumulation expansion of
 // Sec. 3 multiplies S by the number of micro-steps) take the GTAB variant:
@@ -41,13 +47,13 @@
 
 namespace sfk {
 
-// VEC: int64 elements per load (2: 16-byte loads, needs even R and a 16-byte
-//      aligned base); K: ranks per lane per tile; G: lanes per step;
+// VEC: int64 elements per load (2, or 1 where R == 1); K: ranks per lane per
+//      tile; G: lanes per step;
 // WG:  threads per workgroup (WG / G steps per workgroup); CHECK: verify the
 //      data contract into *status; GTAB: partial maxima in the out_increment
-//      rows instead of LDS (any S; G <= 64).
-template <int VEC, int K, int G, int WG, bool CHECK, bool GTAB>
-__global__ __launch_bounds__(WG) void k_frontier(const int64_t* __restrict__ d, int64_t T,
+//      rows instead of LDS (any S; G <= 64); D: stage rows in flight.
+template <int VEC, int K, int G, int WG, bool CHECK, bool GTAB, int D>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(K == 16 && G == 32 ? 4 : 1))) void k_frontier(const int64_t* __restrict__ d, int64_t T,
                                                  int R, int S, int64_t* __restrict__ inc,
                                                  int32_t* __restrict__ lead,
                                                  uint32_t* __restrict__ status)
@@ -65,7 +71,8 @@ __global__ __launch_bounds__(WG) void k_frontier(const int64_t* __restrict__ d, 
 
     const int tid = threadIdx.x;
     const int gl = tid % G;
-    const int j = tid / G;
+    // wave-uniform where a wave holds one step: the row base in SGPRs
+    const int j = G >= 64 ? __builtin_amdgcn_readfirstlane(tid / G) : tid / G;
     const int slot = tid / SUB;
     const bool writer = (tid % SUB) == SUB - 1;
     const int64_t lb = xcd_block();  // XCD-contiguous step runs
@@ -75,52 +82,87 @@ __global__ __launch_bounds__(WG) void k_frontier(const int64_t* __restrict__ d, 
     if (t < T) {  // uniform over the step group
         const int64_t* dt = d + t * (int64_t)S * R;
         for (int r0 = 0; r0 < R; r0 += RT) {
+            // A slot past R takes the last rank pair again (in bounds, the
+            // same cache line): a duplicate of a real key changes no maximum,
+            // and neither does the overlap of a last pair at odd R.
             u64 q[K];
             bool ok[NLD];
+            const int rb = r0 < R - VEC ? r0 : R - VEC;  // a tile of one rank starts one below it
+            const int last = R - VEC - rb;
 #pragma unroll
             for (int l = 0; l < NLD; ++l) {
-                const int r = r0 + (l * G + gl) * VEC;
-                ok[l] = r < R;
+                const int i = (l * G + gl) * VEC;
+                ok[l] = i <= last;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
-                    q[l * VEC + e] = ok[l] ? (kRankMask - (u64)(r + e)) : 0ull;
+                    q[l * VEC + e] = kRankMask - (u64)(rb + (ok[l] ? i : last) + e);
             }
-            int64_t v[K];
-            auto load_row = [&](int s) {
-                const int64_t* row = dt + (int64_t)s * R + r0;
-                // A lane slot past R reads the tile's first rank instead (in
-                // bounds, no branch).  Its key starts with rank field 0, so it
-                // tracks that rank's prefix with a key strictly below the
-                // rank's own key and can never be the maximum.
+            int64_t v[D][K];
+            auto load_row = [&](int c, int s) {
+                const int64_t* row = dt + (int64_t)s * R + rb;
 #pragma unroll
                 for (int l = 0; l < NLD; ++l) {
-                    const int idx = ok[l] ? (l * G + gl) * VEC : 0;
+                    const uint32_t idx = (uint32_t)(ok[l] ? (l * G + gl) * VEC : last);
                     if (VEC == 2) {
-                        const v2i64 x = __builtin_nontemporal_load(reinterpret_cast<const v2i64*>(row + idx));
-                        v[2 * l] = x.x;
-                        v[2 * l + 1] = x.y;
+                        const v2i64_a8 x = __builtin_nontemporal_load(reinterpret_cast<const v2i64_a8*>(row + idx));
+                        v[c][2 * l] = x.x;
+                        v[c][2 * l + 1] = x.y;
                     } else {
-                        v[l] = __builtin_nontemporal_load(row + idx);
+                        v[c][l] = __builtin_nontemporal_load(row + idx);
                     }
                 }
             };
-            load_row(0);
-            for (int s = 0; s < S; ++s) {
-                u64 m = 0;
+            u64 m;
+            auto advance = [&](int c) {
+                m = 0;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    q[k] += (u64)v[k] << kRankBits;
+                    q[k] += (u64)v[c][k] << kRankBits;
                     m = umax64(m, q[k]);
-                    if (CHECK) dhi |= (uint32_t)((u64)v[k] >> 32);
+                    if (CHECK) dhi |= (uint32_t)((u64)v[c][k] >> 32);
                 }
                 if (CHECK) khi |= (uint32_t)(m >> 32);
-                if (s + 1 < S) load_row(s + 1);
+            };
+            auto reduce = [&](int s) {
                 m = group_max<SUB>(m);
                 if (writer) {
                     // GTAB: the step's own out_increment row, read back by
                     // the same lane only until the decode below
                     u64* p = GTAB ? reinterpret_cast<u64*>(inc) + t * S + s : &tab[slot * S + s];
                     *p = (r0 == 0) ? m : umax64(*p, m);
+                }
+            };
+            if constexpr (D == 1) {
+                load_row(0, 0);
+                for (int s = 0; s < S; ++s) {
+                    advance(0);
+                    if (s + 1 < S) load_row(0, s + 1);
+                    reduce(s);
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < D; ++c)
+                    if (c < S) load_row(c, c);
+                int s = 0;
+                // row s + D is always there: no branch between the loads, so
+                // each stage waits for its own row only
+                for (; s + 2 * D <= S; s += D) {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        advance(c);
+                        load_row(c, s + c + D);
+                        reduce(s + c);
+                    }
+                }
+                for (; s < S; s += D) {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        if (s + c < S) {
+                            advance(c);
+                            if (s + c + D < S) load_row(c, s + c + D);
+                            reduce(s + c);
+                        }
+                    }
                 }
             }
         }
@@ -183,47 +225,94 @@ struct FrontierVariant {
     int per_cu;  // resident workgroups per CU to allow (0: no cap)
 };
 
-template <int VEC, bool CHECK, int K, int G, int WG, bool GTAB = false>
+template <bool CHECK, int K, int G, int WG, bool GTAB = false, int D = 1, int VEC = 2>
 FrontierVariant variant(int per_cu)
 {
-    return FrontierVariant{reinterpret_cast<const void*>(&k_frontier<VEC, K, G, WG, CHECK, GTAB>),
+    return FrontierVariant{reinterpret_cast<const void*>(&k_frontier<VEC, K, G, WG, CHECK, GTAB, D>),
                            K, G, WG, per_cu};
 }
 
-// Launch shape by rank count, measured on MI355X over R = 16 .. 16384.
+// Launch shape by rank count, measured on MI355X over R = 8 .. 32768.
 // Wide per-lane tiles (K = 32 ranks, about 250 VGPRs) and few resident
-// workgroups per CU read HBM fastest for large R: fewer concurrent step
-// streams, each with up to 32 KB of loads in flight per wave.  A tile wider
-// than R costs no HBM traffic (lane slots past R re-read a cached rank).
-template <int VEC, bool CHECK>
-FrontierVariant pick_frontier(int R)
+// workgroups per CU read HBM fastest where R fills them: fewer concurrent
+// step streams, each with up to 32 KB of loads in flight per wave.  Lane slots
+// past R cost no HBM traffic but hold a wave's issue slots, so ranks that
+// leave half of such a tile empty take one closer to R (R = 700: 6.1 -> 7.0
+// TB/s, 2049: 2.6 -> 7.0, 1030: 5.0 -> 5.8); near the full tile the wide ones
+// stay ahead once the rows of all steps reach 32 MB (R = 1024: 7.07 against
+// 6.80 TB/s; below, at 16 MB, 6.2 against 6.3, at 4 MB 3.0 against 4.8).
+template <bool CHECK>
+FrontierVariant pick_frontier(int R, int64_t row_bytes)
 {
-    if (R <= 8) return variant<VEC, CHECK, 2, 4, 64>(0);
-    if (R <= 16) return variant<VEC, CHECK, 2, 8, 128>(0);
-    if (R <= 32) return variant<VEC, CHECK, 4, 8, 128>(0);
-    if (R <= 64) return variant<VEC, CHECK, 4, 16, 256>(6);
-    if (R <= 128) return variant<VEC, CHECK, 8, 32, 256>(6);
-    if (R <= 256) return variant<VEC, CHECK, 16, 32, 256>(4);
-    if (R <= 512) return variant<VEC, CHECK, 4, 256, 256>(0);
-    if (R <= 1024) return variant<VEC, CHECK, 32, 64, 256>(6);
-    if (R <= 2048) return variant<VEC, CHECK, 8, 512, 512>(0);
-    if (R <= 4096) return variant<VEC, CHECK, 32, 256, 256>(0);
-    return variant<VEC, CHECK, 32, 64, 64>(3);
+    const bool many = row_bytes >= 32 << 20;
+    if (R == 1) return variant<CHECK, 2, 4, 64, false, 1, 1>(0);
+    if (R <= 8) return variant<CHECK, 2, 4, 64>(0);
+    if (R <= 16) return variant<CHECK, 2, 8, 128>(0);
+    if (R <= 32) return variant<CHECK, 4, 8, 128>(0);
+    if (R <= 64) return variant<CHECK, 4, 16, 256>(6);
+    if (R <= 128) return variant<CHECK, 8, 32, 256>(6);
+    if (R <= 256) return variant<CHECK, 16, 32, 256>(4);
+    if (R <= 512) return variant<CHECK, 4, 256, 256>(0);
+    if (R <= 1024) return R > 896 && many ? variant<CHECK, 32, 64, 256>(6) : variant<CHECK, 4, 256, 256>(0);
+    if (R <= 1792) return variant<CHECK, 4, 512, 512, false, 4>(0);
+    if (R <= 2048) return variant<CHECK, 8, 512, 512>(0);
+    if (R <= 4096) return R > 3840 && many ? variant<CHECK, 32, 256, 256>(0) : variant<CHECK, 8, 512, 512>(0);
+    if (R <= 5120) return variant<CHECK, 8, 1024, 1024, false, 2>(0);
+    return variant<CHECK, 32, 64, 64>(3);
+}
+
+// The deep shapes: the step over as many lanes as a workgroup takes, one
+// tile up to 16384 ranks.
+template <bool CHECK>
+FrontierVariant pick_frontier_deep(int R)
+{
+    if (R <= 8) return variant<CHECK, 2, 4, 64, false, 8>(0);
+    if (R <= 16) return variant<CHECK, 2, 8, 64, false, 8>(0);
+    if (R <= 32) return variant<CHECK, 2, 16, 64, false, 8>(0);
+    if (R <= 64) return variant<CHECK, 2, 32, 64, false, 8>(0);
+    if (R <= 128) return variant<CHECK, 2, 64, 64, false, 8>(0);
+    if (R <= 256) return variant<CHECK, 2, 128, 128, false, 8>(0);
+    if (R <= 512) return variant<CHECK, 2, 256, 256, false, 8>(0);
+    if (R <= 1024) return variant<CHECK, 2, 512, 512, false, 8>(0);
+    if (R <= 2048) return variant<CHECK, 4, 512, 512, false, 4>(0);
+    if (R <= 4096) return variant<CHECK, 4, 1024, 1024, false, 4>(0);
+    if (R <= 8192) return variant<CHECK, 8, 1024, 1024, false, 2>(0);
+    return variant<CHECK, 16, 1024, 1024>(0);
+}
+
+// Where the deep shapes are the faster ones (measured on MI355X).  Past 4096
+// ranks the wide shape gives a step one wave, so below about 400 steps the
+// chip idles (16384 ranks x 12 stages: 64 steps 87 -> 31 us, 256 steps 99 ->
+// 63, 512 steps 115 -> 119).  Up to 4096 ranks the rows in flight are worth
+// their registers while the stage rows of all steps are within 4 MB and there
+// are more stages than rows in flight (130 x 100 stages: 1024 steps 66 -> 28
+// us, 4096 steps 88 -> 80; 40 x 8: 3.6 -> 4.0); from 513 ranks twice as many
+// stages (1024 x 8: 4.3 against 5.1); at 129 to 256 ranks they also win at
+// few stages up to 2 MB (250 x 8: 256 steps 5.7 -> 4.7 us, 4096 steps 11.5 ->
+// 14.5).
+static bool deep_steps(int64_t T, int R, int S)
+{
+    const int64_t row = T * R * 8;
+    if (R == 1) return false;
+    if (R > 4096) return T < 400;
+    if (R > 128 && R <= 256 && row <= 2 << 20) return true;
+    return S > (R > 512 ? 16 : 8) && row <= 4 << 20;
 }
 
 // Stage counts whose LDS table would exceed what a workgroup may hold: the
 // shapes with one group of at most 64 lanes per step, with the table in the
 // out_increment rows.
-template <int VEC, bool CHECK>
+template <bool CHECK>
 FrontierVariant pick_frontier_gtab(int R)
 {
-    if (R <= 8) return variant<VEC, CHECK, 2, 4, 64, true>(0);
-    if (R <= 16) return variant<VEC, CHECK, 2, 8, 128, true>(0);
-    if (R <= 32) return variant<VEC, CHECK, 4, 8, 128, true>(0);
-    if (R <= 64) return variant<VEC, CHECK, 4, 16, 256, true>(6);
-    if (R <= 128) return variant<VEC, CHECK, 8, 32, 256, true>(6);
-    if (R <= 256) return variant<VEC, CHECK, 16, 32, 256, true>(4);
-    return variant<VEC, CHECK, 32, 64, 64, true>(3);
+    if (R == 1) return variant<CHECK, 2, 4, 64, true, 1, 1>(0);
+    if (R <= 8) return variant<CHECK, 2, 4, 64, true>(0);
+    if (R <= 16) return variant<CHECK, 2, 8, 128, true>(0);
+    if (R <= 32) return variant<CHECK, 4, 8, 128, true>(0);
+    if (R <= 64) return variant<CHECK, 4, 16, 256, true>(6);
+    if (R <= 128) return variant<CHECK, 8, 32, 256, true>(6);
+    if (R <= 256) return variant<CHECK, 16, 32, 256, true>(4);
+    return variant<CHECK, 32, 64, 64, true>(3);
 }
 
 // Largest S whose LDS table of partial maxima (16 slots of S keys in the
@@ -248,15 +337,13 @@ static int frontier_launch(const int64_t* durations, int64_t T, int32_t R, int32
                    !disjoint(status, 4, out_increment, ni) || !disjoint(status, 4, out_leader, nl)))
         return SF_EINVAL;
 
-    const bool vec2 = (R % 2 == 0) && aligned(durations, 16);
     const bool gtab = S > kFrontierLdsS;
-    FrontierVariant v;
-    if (gtab)
-        v = status ? (vec2 ? pick_frontier_gtab<2, true>(R) : pick_frontier_gtab<1, true>(R))
-                   : (vec2 ? pick_frontier_gtab<2, false>(R) : pick_frontier_gtab<1, false>(R));
-    else
-        v = status ? (vec2 ? pick_frontier<2, true>(R) : pick_frontier<1, true>(R))
-                   : (vec2 ? pick_frontier<2, false>(R) : pick_frontier<1, false>(R));
+    const bool deep = !gtab && deep_steps(T, R, S);
+    const int64_t row = T * R * 8;
+    const FrontierVariant v =
+        gtab   ? (status ? pick_frontier_gtab<true>(R) : pick_frontier_gtab<false>(R))
+        : deep ? (status ? pick_frontier_deep<true>(R) : pick_frontier_deep<false>(R))
+               : (status ? pick_frontier<true>(R, row) : pick_frontier<false>(R, row));
     const int spw = v.WG / v.G;
     const int sub = v.G < 64 ? v.G : 64;
     const int64_t blocks = (T + spw - 1) / spw;

@@ -213,6 +213,34 @@ def test_frontier_misaligned_base_uses_narrow_loads(sf):
     np.testing.assert_array_equal(lead.cpu().numpy(), ol)
 
 
+@pytest.mark.parametrize("R,S,T", [
+    (2, 9, 33), (3, 17, 40), (8, 25, 17), (15, 9, 40), (33, 16, 9), (65, 31, 5), (127, 9, 3), (129, 2, 9), (255, 17, 3),
+    (257, 9, 5), (511, 24, 3), (513, 8, 4), (513, 17, 4), (897, 5, 4700), (1023, 18, 3), (1025, 8, 5), (1793, 3, 4),
+    (1791, 17, 2), (2047, 33, 2), (2049, 6, 3), (3841, 2, 1100), (4095, 17, 3), (4097, 7, 399), (4097, 7, 401),
+    (5121, 2, 400), (8191, 5, 3), (8193, 4, 399), (12289, 2, 400), (16385, 3, 2), (32769, 3, 2), (65535, 2, 2)])
+def test_frontier_shape_rules(sf, R, S, T):
+    """Both sides of every rule that picks a launch shape, and the edges of
+    the shapes: odd rank counts, whose last pair overlaps the one before (also
+    a tile of one rank), stage counts around the rows kept in flight, an 8-byte
+    aligned base, the largest prefix at the last ranks, and ties."""
+    rng = np.random.Generator(np.random.PCG64(R * 31 + S))
+    d = rng.integers(0, 1000, size=(T, S, R), dtype=np.int64)
+    d[0::3, S // 2, R - 1] += 10**6
+    d[1::3, 0, R - 2] += 10**6
+    d[1::6, 0, R - 1] += 10**7
+    d[2::6] = 7
+    oi, ol = oracle.frontier(d)
+    flat = torch.zeros(T * S * R + 1, dtype=torch.int64, device=DEV)
+    view = flat[1:].view(T, S, R)
+    view.copy_(torch.from_numpy(d))
+    print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    for inc, lead in (sf.sf_frontier(view), sf.sf_frontier_checked(view, status=status)[:2]):
+        np.testing.assert_array_equal(inc.cpu().numpy(), oi)
+        np.testing.assert_array_equal(lead.cpu().numpy(), ol)
+    assert int(status) == 0
+
+
 def test_frontier_chunks_compose(sf):
     """Step-axis chunks written into one output equal a single call."""
     T, S, R = 101, 12, 640
