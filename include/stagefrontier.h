@@ -240,10 +240,10 @@ int sf_exposure_gain(const int64_t* durations, const int64_t* baseline, int64_t 
  *
  *   durations      [T][S][R] int64 ns (as for sf_frontier).
  *   T, R, S        0 <= T <= INT32_MAX, 1 <= R <= SF_MAX_R, 1 <= S.  A
- *                  step's values are held on chip up to 16384 ranks (up to
- *                  32768 for even R with a 16-byte aligned base); beyond
- *                  that a kernel re-reads them from global memory at every
- *                  select pass (slower, same results).
+ *                  step's values are held on chip up to 32768 ranks (past
+ *                  16384 while durations and the spread of the prefixes stay
+ *                  below 2^32 ns); beyond that a kernel re-reads them from
+ *                  global memory at every select pass (slower, same results).
  *                  T == 0 is a no-op.
  *   out_lag        [T][S] int64 ns, >= 0.
  *   out_lag_inc    [T][S] int64 ns.

@@ -99,17 +99,39 @@ __device__ __forceinline__ int held_first_bin(uint32_t u, int lo) { return (int)
 // once).  Both compute the same lower median of the same values.
 constexpr int64_t kRedo = INT64_MIN;  // outputs are >= 0 under the data contract
 
+//
+// The narrow pass takes any R >= 2: its 16-byte loads need only the 8-byte
+// alignment of the ranks.  Slots past R (and, where R is odd, the first slot
+// of the last pair, which overlaps the one before) load the last pair again
+// and, once the boundary's maximum is known, hold that maximum: copies of the
+// largest value do not move the lower median, so the select needs no rank
+// tests.  Whether a slot is one is worked out from R where it is asked,
+// behind an opaque copy of R: hoisted out of the stage loop the tests take an
+// SGPR pair per load (2 to 8 spilled VGPRs at the 64-VGPR budget).  The
+// 64-bit shapes are faster with the hoisted tests (1024 ranks 98 against
+// 111 us, their registers grow from 96 to 125).
+//
+// SPLIT (the lag with few steps): a step's stages are shared by several
+// workgroups of SC stages each.  Each first sums the durations of the stages
+// before its own (without selects), and resolves the boundary before its
+// first once more for the increment.  A boundary costs 2 to 3 us in series
+// (LDS latency and barriers), its durations a re-read from the caches: 429
+// ranks x 220 stages x 128 steps 616 -> 222 us.
+constexpr int kRedoRows = 8;  // steps whose markers one workgroup of the REDO launch looks at
+
 template <bool PREFIX, int VEC, int K, int WG, int LCAP, bool PUBU, bool FULL, bool NARROW,
-          bool REDO>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K <= 16 ? 8 : 4))) void k_median_spread(const int64_t* __restrict__ d, int64_t T,
+          bool REDO, bool SPLIT>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K <= 16 ? 8 : WG == 768 ? 6 : 4) : 4))) void k_median_spread(const int64_t* __restrict__ d, int64_t T,
                                                       int R, int S, int64_t* __restrict__ out,
-                                                      int64_t* __restrict__ out_inc)
+                                                      int64_t* __restrict__ out_inc, int SC)
 {
     static_assert(K % VEC == 0 && WG % 64 == 0 && WG / 64 <= 16, "shape");
-    static_assert(!NARROW || (VEC == 2 && !REDO), "the narrow pass takes 16-byte loads");
+    static_assert(!NARROW || !REDO, "the narrow pass hands over");
+    static_assert(!SPLIT || (PREFIX && !NARROW && !REDO), "SPLIT: the 64-bit lag");
     typedef typename std::conditional<NARROW, uint32_t, u64>::type V;
     constexpr int NW = WG / 64;
-    constexpr int NLD = K / VEC;
+    constexpr int NLD = NARROW ? K / 2 : K / VEC;
+    constexpr bool ODD = NARROW && VEC == 1;  // odd R: the narrow pass loads pairs all the same
     constexpr bool SCAN_ALL = !PREFIX && NW > 1;
     constexpr int NH = SCAN_ALL ? 3 : 2;  // histograms
     // per-wave max/min partials, double-buffered by stage parity: a wave
@@ -125,11 +147,41 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS slots in SGPRs
-    const int64_t t = xcd_block();
-    if (t >= T) return;  // uniform over the workgroup (the grid is T)
-    if (REDO && out[t * S] != kRedo) return;  // a step the narrow pass resolved
+    int s0 = 0, sb = 0, s1 = S;  // own stages [s0, s1), the walk starts at sb
+    int64_t unit = xcd_block();
+    if (SPLIT) {
+        const int nc = (S + SC - 1) / SC;
+        const int64_t b = unit;
+        unit = b / nc;
+        s0 = (int)(b - unit * nc) * SC;
+        s1 = min(S, s0 + SC);
+        sb = s0 > 0 ? s0 - 1 : 0;
+    }
+    uint32_t todo = 0;  // REDO: the steps of this workgroup that the narrow pass handed over
+    if (REDO) {
+        unit = (int64_t)blockIdx.x * kRedoRows;
+        todo = (uint32_t)__ballot(lane < kRedoRows && unit + lane < T && out[(unit + lane) * S] == kRedo);
+    }
+    for (;;) {  // once, and for REDO once per handed-over step
+    int64_t t = unit;
+    if (REDO) {
+        if (todo == 0) return;  // uniform over the workgroup
+        t = unit + __builtin_ctz(todo);
+        todo &= todo - 1;
+    }
+    if (t >= T) return;  // uniform over the workgroup
     const int64_t* dt = d + t * (int64_t)S * R;
 
+    // R, but unknown to the compiler to be loop-invariant
+    auto opaque_R = [&]() {
+        int x = R;
+        asm volatile("" : "+s"(x));
+        return x;
+    };
+    // NARROW: slot k holds a rank of its own
+    auto real = [&](int k, int Rv) {
+        return FULL || (k / 2 * WG + tid) * 2 < (ODD && (k & 1) == 0 ? Rv - 1 : Rv);
+    };
     bool ok[NLD];
     int idx[NLD];
 #pragma unroll
@@ -145,7 +197,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
 #pragma unroll
         for (int l = 0; l < NLD; ++l) {
             if (VEC == 2) {
-                const v2i64 x = __builtin_nontemporal_load(reinterpret_cast<const v2i64*>(row + idx[l]));
+                const v2i64_a8 x = __builtin_nontemporal_load(reinterpret_cast<const v2i64_a8*>(row + idx[l]));
                 nx[l * VEC] = x.x;
                 nx[l * VEC + VEC - 1] = x.y;
             } else {
@@ -153,11 +205,39 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
             }
         }
     };
-    if (!NARROW) load_stage(0);
-
     V P[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) P[k] = 0;
+    if (SPLIT) {
+        // the stages before sb, several rows in flight
+        constexpr int U = K >= 16 ? 1 : 16 / K;
+        int j = 0;
+        auto sum_rows = [&](auto n) {
+            int64_t x[n()][K];
+#pragma unroll
+            for (int u = 0; u < n(); ++u) {
+                const int64_t* row = dt + (int64_t)(j + u) * R;
+#pragma unroll
+                for (int l = 0; l < NLD; ++l) {
+                    if (VEC == 2) {
+                        const v2i64_a8 y = *reinterpret_cast<const v2i64_a8*>(row + idx[l]);
+                        x[u][l * VEC] = y.x;
+                        x[u][l * VEC + VEC - 1] = y.y;
+                    } else {
+                        x[u][l] = row[idx[l]];
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < n(); ++u)
+#pragma unroll
+                for (int k = 0; k < K; ++k) P[k] += (V)x[u][k];
+            j += n();
+        };
+        while (j + U <= sb) sum_rows(std::integral_constant<int, U>{});
+        while (j < sb) sum_rows(std::integral_constant<int, 1>{});
+    }
+    if (!NARROW) load_stage(sb);
     for (int i = tid; i < NH * kLagWords; i += WG) (&hist[0][0])[i] = 0;
     if (tid == 0) {
         list_n = 0;
@@ -168,7 +248,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
     int cur = 0;  // the histogram of the next pass (clear)
     const uint32_t target = (uint32_t)((R - 1) / 2);
 
-    for (int s = 0; s < S; ++s) {
+    for (int s = sb; s < s1; ++s) {
         u64 lmax = 0, lmin = ~0ull;
         if constexpr (NARROW) {
             // the stage's 16-byte loads in CH chunks, each consumed before
@@ -177,7 +257,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
             // (with the select's tests in 32 bits this fits the 64-VGPR
             // budget; measured at 16384 ranks 3% faster than two at a time,
             // which the 64-bit tests forced); at 32 values, two at a time
-            constexpr int CH = PREFIX ? (K == 16 ? 2 : NLD / 2) : (K <= 32 ? 2 : NLD / 4);
+            constexpr int CH = WG == 768 ? NLD / 4 : PREFIX ? (K == 16 ? 2 : NLD / 2) : 2;
             // the stage row through a buffer resource: its base in SGPRs, a
             // lane's offset in one VGPR (FULL: the same for every load)
             const auto rs = buffer_rsrc(dt + (int64_t)s * R, (uint32_t)R * 8u);
@@ -185,26 +265,24 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
             bool wide = false;  // wave-uniform: some value of the wave left 32 bits
 #pragma unroll
             for (int ch = 0; ch < CH; ++ch) {
+                const int Rv = opaque_R();
                 uint32_t w = 0;
                 v2i64 xs[NLD / CH];
 #pragma unroll
                 for (int l = 0; l < NLD / CH; ++l) {
                     const int ll = ch * (NLD / CH) + l;
                     xs[l] = FULL ? buffer_load16_nt(rs, (uint32_t)tid * 16u, (uint32_t)(ll * WG * 16))
-                                 : buffer_load16_nt(rs, (uint32_t)idx[ll] * 8u, 0u);
+                                 : buffer_load16_nt(rs, (uint32_t)min((ll * WG + tid) * 2, Rv - 2) * 8u, 0u);
                 }
                 __builtin_amdgcn_sched_barrier(0);  // the chunk's loads all in flight first
 #pragma unroll
                 for (int l = 0; l < NLD / CH; ++l) {
-                    // a slot pair past R (re-reading the row's first pair)
-                    // keeps 0 and is left out of every reduction and pass
-                    const bool okl = ok[ch * (NLD / CH) + l];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
                         const int k = (ch * (NLD / CH) + l) * 2 + e;
                         const u64 x = (u64)(e == 0 ? xs[l].x : xs[l].y);
-                        const uint32_t lo = okl ? (uint32_t)x : 0u;
-                        w |= okl ? (uint32_t)(x >> 32) : 0u;
+                        const uint32_t lo = (uint32_t)x;
+                        w |= (uint32_t)(x >> 32);
                         if (PREFIX) {
                             const uint32_t np = (uint32_t)P[k] + lo;
                             w |= np < lo ? 1u : 0u;  // carry
@@ -212,8 +290,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
                         } else {
                             P[k] = lo;
                         }
-                        mx = max(mx, okl ? (uint32_t)P[k] : 0u);
-                        mn = min(mn, okl ? (uint32_t)P[k] : ~0u);
+                        // the lag's other slots carry on from the last
+                        // boundary's maximum: past the others, not below
+                        mx = max(mx, !PREFIX || real(k, Rv) ? (uint32_t)P[k] : 0u);
+                        mn = min(mn, (uint32_t)P[k]);
                     }
                 }
                 wide = wide || __ballot(w != 0) != 0;
@@ -234,7 +314,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
                     lmin = umin64(lmin, P[k]);
                 }
             }
-            if (s + 1 < S) load_stage(s + 1);
+            if (s + 1 < s1) load_stage(s + 1);
             // block max and min (min as the max of complements)
             lmax = group_max<64>(lmax);
             lmin = ~group_max<64>(~lmin);
@@ -258,8 +338,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
         if (NARROW) wide_step = wide_step || (F >> 32) != 0;
         // rebase: from here on P holds u = P - Pmin (the minimum is 0)
         const u64 range = F - Pmin;
+        const int Rs = NARROW ? opaque_R() : R;
 #pragma unroll
-        for (int k = 0; k < K; ++k) P[k] -= (V)Pmin;
+        for (int k = 0; k < K; ++k) P[k] = !NARROW || real(k, Rs) ? P[k] - (V)Pmin : (V)range;
         u64 um = 0;            // u of the median (0 when every u is 0)
         bool written = false;  // the lane holding the median wrote the outputs
         if (range != 0) {
@@ -281,13 +362,20 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
                 } else if (first) {
                     // one plain atomic per value (3-4% faster than adding
                     // runs of equal bins among a lane's values at once)
+                    // NARROW: the copies of the maximum would serialise on one
+                    // word, so one lane adds them all (every pass counts them)
+                    if (NARROW && !FULL && tid == 0)
+                        atomicAdd(&h[held_first_bin((V)range, lo)], (uint32_t)(K * WG - R));
+                    // (the tests of the rebase over again where they would
+                    // spill: 24576 ranks, 678 against 379 us)
+                    const int Rh = WG == 768 ? opaque_R() : Rs;
 #pragma unroll
                     for (int k = 0; k < K; ++k)
-                        if (ok[k / VEC]) atomicAdd(&h[held_first_bin(P[k], lo)], 1u);
+                        if (NARROW ? real(k, Rh) : ok[k / VEC]) atomicAdd(&h[held_first_bin(P[k], lo)], 1u);
                 } else {
 #pragma unroll
                     for (int k = 0; k < K; ++k)
-                        sel_hist_add(h, ok[k / VEC] ? held_bin(P[k], lo, hi, prefix) : -1);
+                        sel_hist_add(h, NARROW || ok[k / VEC] ? held_bin(P[k], lo, hi, prefix) : -1);
                 }
                 first = false;
                 lds_barrier();
@@ -357,7 +445,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
                     } else {
 #pragma unroll
                         for (int k = 0; k < K; ++k) {
-                            if (ok[k / VEC] && held_match(P[k], hi, prefix)) {
+                            if ((NARROW || ok[k / VEC]) && held_match(P[k], hi, prefix)) {
                                 u = P[k];
                                 holder = true;
                             }
@@ -365,8 +453,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
                     }
                     if (holder) {
                         const int64_t L = (int64_t)(range - u);
-                        out[t * S + s] = L;
-                        if (PREFIX) out_inc[t * S + s] = L - lag_sh[(s + 1) & 1];
+                        if (!SPLIT || s >= s0) {
+                            out[t * S + s] = L;
+                            if (PREFIX) out_inc[t * S + s] = L - lag_sh[(s + 1) & 1];
+                        }
                         lag_sh[s & 1] = L;
                     }
                     written = true;
@@ -378,7 +468,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
                     uint32_t cand = 0;  // bit k: P[k] is a candidate
 #pragma unroll
                     for (int k = 0; k < K; ++k)
-                        cand |= (ok[k / VEC] && held_match(P[k], hi, prefix)) ? (1u << k) : 0u;
+                        cand |= ((NARROW || ok[k / VEC]) && held_match(P[k], hi, prefix)) ? (1u << k) : 0u;
                     const uint32_t nc = (uint32_t)__popc(cand);
                     const uint32_t incl2 = wave_scan_incl(nc);
                     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl2, 63);
@@ -407,8 +497,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
         }
         if (!written && tid == 0) {
             const int64_t L = (int64_t)(range - um);
-            out[t * S + s] = L;
-            if (PREFIX) out_inc[t * S + s] = L - lag_sh[(s + 1) & 1];
+            if (!SPLIT || s >= s0) {
+                out[t * S + s] = L;
+                if (PREFIX) out_inc[t * S + s] = L - lag_sh[(s + 1) & 1];
+            }
             lag_sh[s & 1] = L;
         }
         // lag_sh[s & 1] is read at stage s + 1, after its reduction barrier
@@ -416,6 +508,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW && K 
     if (NARROW) {
         __syncthreads();  // after every output write of the step (global stores)
         if (wide_step && tid == 0) out[t * S] = kRedo;
+    }
+    if (!REDO) return;
+    __syncthreads();  // the LDS tables are set up for the next step
     }
 }
 
@@ -447,9 +542,12 @@ __global__ __launch_bounds__(kStreamWG) void k_median_stream(const int64_t* __re
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int64_t t = blockIdx.x;
+    // REDO: the steps of this workgroup that the narrow pass handed over
+    const int64_t unit = REDO ? (int64_t)blockIdx.x * kRedoRows : blockIdx.x;
+    uint32_t todo = REDO ? (uint32_t)__ballot(lane < kRedoRows && unit + lane < T && out[(unit + lane) * S] == kRedo) : 1u;
+    for (; todo != 0; todo &= todo - 1) {
+    const int64_t t = unit + __builtin_ctz(todo);
     if (t >= T) return;
-    if (REDO && out[t * S] != kRedo) return;  // a step the narrow pass resolved
     const int64_t* dt = d + t * (int64_t)S * R;
     for (int i = tid; i < kSelWords; i += kStreamWG) hist[i] = 0;
     int64_t L_prev = 0;
@@ -552,15 +650,17 @@ __global__ __launch_bounds__(kStreamWG) void k_median_stream(const int64_t* __re
         L_prev = (int64_t)(range - um);
         __syncthreads();  // red_max, red_min and the list are rewritten by the next stage
     }
+    }
 }
 
 struct LagVariant {
     const void* fn;
     int WG;
     const void* redo;  // after a narrow pass: the 64-bit kernel for the steps it handed over
+    int redo_WG;
 };
 
-template <bool PREFIX, int VEC, int K, int WG, bool FULL, bool NARROW = false, bool REDO = false>
+template <bool PREFIX, int VEC, int K, int WG, bool FULL, bool NARROW = false, bool REDO = false, bool SPLIT = false>
 const void* lag_kernel()
 {
     // candidate list: a quarter of the slots, at most 4096 values; none when
@@ -569,7 +669,7 @@ const void* lag_kernel()
     constexpr bool PUBU = PREFIX && K == 16 && WG <= 256 && !NARROW;
     static_assert(!(PUBU && FULL), "the PUBU shapes keep the rank tests");
     return reinterpret_cast<const void*>(
-        &k_median_spread<PREFIX, VEC, K, WG, LCAP, PUBU, FULL, NARROW, REDO>);
+        &k_median_spread<PREFIX, VEC, K, WG, LCAP, PUBU, FULL, NARROW, REDO, SPLIT>);
 }
 
 // FULL: R fills the K * WG slots exactly, so no slot needs a rank test
@@ -581,61 +681,101 @@ const void* lag_kernel()
 // (measured at 16384 ranks: 32% faster for the raw spread, 18% for the lag;
 // at 1024 and 4096 ranks the raw spread 9% and 4% faster, the lag 6% slower,
 // so the lag keeps its 64-bit shapes there).
-// More than 16384 ranks: up to 32768 the 32-bit pass with 32 values per
-// lane (16-byte loads), the streaming 64-bit kernel redoing the steps it
-// hands over; beyond that (64 values per lane spill) and with 8-byte loads
-// (odd R or a misaligned base) the streaming kernel alone.
+// More than 16384 ranks: up to 32768 the 32-bit pass with 32 values per lane,
+// the streaming 64-bit kernel redoing the steps it hands over; beyond that
+// the streaming kernel alone.  Up to 24576 ranks 12 waves per step leave two
+// workgroups to a CU at 80 VGPRs each, whose loads and selects overlap (17000
+// ranks x 9 x 1024: the raw spread 379 -> 273 us, the lag 408 -> 340); with a
+// workgroup per CU or less there is nothing to overlap, and 16 waves are
+// faster (the lag, 128 steps: 102 against 107 us).
 template <bool PREFIX, int VEC>
-LagVariant lag_wide(int R)
+LagVariant lag_wide(int64_t T, int R)
 {
-    if constexpr (VEC == 2) {
-        const void* redo = reinterpret_cast<const void*>(&k_median_stream<PREFIX, true>);
-        if (R == 32 * 1024) return LagVariant{lag_kernel<PREFIX, 2, 32, 1024, true, true>(), 1024, redo};
-        if (R < 32 * 1024) return LagVariant{lag_kernel<PREFIX, 2, 32, 1024, false, true>(), 1024, redo};
-    }
-    (void)R;
-    return LagVariant{reinterpret_cast<const void*>(&k_median_stream<PREFIX, false>), kStreamWG,
-                      nullptr};
+    const void* redo = reinterpret_cast<const void*>(&k_median_stream<PREFIX, true>);
+    if (R <= 32 * 768 && T > 256) return LagVariant{lag_kernel<PREFIX, VEC, 32, 768, false, true>(), 768, redo, kStreamWG};
+    if (R < 32 * 1024) return LagVariant{lag_kernel<PREFIX, VEC, 32, 1024, false, true>(), 1024, redo, kStreamWG};
+    if (R == 32 * 1024) return LagVariant{lag_kernel<PREFIX, VEC, 32, 1024, true, true>(), 1024, redo, kStreamWG};
+    return LagVariant{reinterpret_cast<const void*>(&k_median_stream<PREFIX, false>), kStreamWG, nullptr, 0};
 }
 
 template <bool PREFIX, int VEC, int K, int WG>
-LagVariant lag_shape(int R)
+LagVariant lag_shape(int R, bool split)
 {
     constexpr bool pubu = PREFIX && K == 16 && WG <= 256;
-    if constexpr (VEC == 2 && K == 16 && (WG >= 512 || !PREFIX)) {
-        if (R == K * WG)
-            return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true, true>(), WG,
-                              lag_kernel<PREFIX, VEC, K, WG, false, false, true>()};
+    if constexpr (PREFIX) {
+        if (split) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false, false, false, true>(), WG, nullptr, 0};
     }
-    if constexpr (!pubu) {
-        if (R == K * WG) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true>(), WG, nullptr};
+    if constexpr (K == 16 && (WG >= 512 || !PREFIX)) {
+        const void* redo = lag_kernel<PREFIX, VEC, K, WG, false, false, true>();
+        if (R == K * WG) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true, true>(), WG, redo, WG};
+        return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false, true>(), WG, redo, WG};
+    } else {
+        if constexpr (!pubu) {
+            if (R == K * WG) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true>(), WG, nullptr, 0};
+        }
+        return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false>(), WG, nullptr, 0};
     }
-    return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false>(), WG, nullptr};
 }
 
 // One step per workgroup with all R prefixes in registers, as few waves as
 // the registers allow: a wave spends less time at barriers than a lane does
 // on 4x the prefixes (measured on the 128- to 16384-rank workloads).
 template <bool PREFIX, int VEC>
-LagVariant pick_lag(int R)
+LagVariant pick_lag(int64_t T, int R, bool split)
 {
-    if (R <= 128) return lag_shape<PREFIX, VEC, 2, 64>(R);
-    if (R <= 256) return lag_shape<PREFIX, VEC, 4, 64>(R);
-    if (R <= 512) return lag_shape<PREFIX, VEC, 8, 64>(R);
-    if (R <= 1024) return lag_shape<PREFIX, VEC, 16, 64>(R);
-    if (R <= 2048) return lag_shape<PREFIX, VEC, 16, 128>(R);
-    if (R <= 4096) return lag_shape<PREFIX, VEC, 16, 256>(R);
-    if (R <= 8192) return lag_shape<PREFIX, VEC, 16, 512>(R);
-    if (R <= 16384) return lag_shape<PREFIX, VEC, 16, 1024>(R);
-    return lag_wide<PREFIX, VEC>(R);  // R <= SF_MAX_R
+    if (R <= 128) return lag_shape<PREFIX, VEC, 2, 64>(R, split);
+    if (R <= 256) return lag_shape<PREFIX, VEC, 4, 64>(R, split);
+    if (R <= 512) return lag_shape<PREFIX, VEC, 8, 64>(R, split);
+    if (R <= 1024) return lag_shape<PREFIX, VEC, 16, 64>(R, split);
+    if (R <= 2048) return lag_shape<PREFIX, VEC, 16, 128>(R, split);
+    if (R <= 4096) return lag_shape<PREFIX, VEC, 16, 256>(R, split);
+    if (R <= 8192) return lag_shape<PREFIX, VEC, 16, 512>(R, split);
+    if (R <= 16384) return lag_shape<PREFIX, VEC, 16, 1024>(R, split);
+    return lag_wide<PREFIX, VEC>(T, R);  // R <= SF_MAX_R
 }
 
-// the narrow pass, then (if it has one) the 64-bit pass over the steps it
-// handed over
-static int launch_lag(const LagVariant& v, int64_t T, void** args, sf_stream_t stream)
+// Waves that a split lag aims at, and below which the raw spread takes rows
+// for steps.
+constexpr int64_t kLagWaves = 4096;
+constexpr int64_t kSpreadWaves = 8192;
+
+// The narrow pass, then (if it has one) the 64-bit pass over the steps it
+// handed over.
+//
+// Few steps: the stages of the raw spread are independent rows, so they
+// become steps of one stage each (measured: 16 steps 5 to 60 times faster,
+// 1024 steps of 1024 ranks 39 -> 21 us; past 4096 ranks always, 8192 x 12 x
+// 1024 141 -> 126; at 8192 waves and up to 512 ranks still 72 -> 65, at 1024
+// ranks 99 -> 103).  The lag shares a step's stages among workgroups, where
+// that makes at least four of them, or two past 4096 ranks (128 steps: 1024
+// ranks x 8 32 -> 13 us, 16384 x 12 97 -> 73; 1024 steps of 1264 ranks,
+// two each: 42 -> 48; odd ranks past 512, loaded 8 bytes at a time, at least
+// six: 1023 x 8, four of them 38 -> 40, eight 36 -> 31).
+template <bool PREFIX>
+static int launch_lag(const int64_t* d, int64_t T, int R, int S, int64_t* out, int64_t* out_inc,
+                      sf_stream_t stream)
 {
-    int rc = launch(v.fn, dim3((unsigned)T), dim3(v.WG), args, 0, stream);
-    if (rc == SF_OK && v.redo) rc = launch(v.redo, dim3((unsigned)T), dim3(v.WG), args, 0, stream);
+    const int64_t waves = T * (R <= 1024 ? 1 : R >= 16384 ? 16 : (R + 1023) / 1024);
+    int64_t units = 1;
+    int SC = S;
+    if (PREFIX) {
+        units = kLagWaves / waves;
+        if (units > S) units = S;
+        if (R > 16384 || units < (R > 4096 ? 2 : R > 512 && (R & 1) ? 6 : 4)) units = 1;
+        SC = (int)((S + units - 1) / units);
+        units = (S + SC - 1) / SC;
+    } else if ((waves < kSpreadWaves || R > 4096 || (R <= 512 && waves <= kSpreadWaves * 3 / 2)) &&
+               T <= INT32_MAX / S) {
+        T *= S;
+        S = SC = 1;
+    }
+    const bool split = units > 1;
+    const bool vec2 = (R & 1) == 0;
+    const LagVariant v = vec2 ? pick_lag<PREFIX, 2>(T, R, split) : pick_lag<PREFIX, 1>(T, R, split);
+    void* args[] = {(void*)&d, (void*)&T, (void*)&R, (void*)&S, (void*)&out, (void*)&out_inc, (void*)&SC};
+    int rc = launch(v.fn, dim3((unsigned)(T * units)), dim3(v.WG), args, 0, stream);
+    if (rc == SF_OK && v.redo)
+        rc = launch(v.redo, dim3((unsigned)((T + kRedoRows - 1) / kRedoRows)), dim3(v.redo_WG), args, 0, stream);
     return rc;
 }
 
@@ -657,12 +797,7 @@ SF_API int sf_frontier_lag(const int64_t* durations, int64_t T, int32_t R, int32
     if (!disjoint(durations, nd, out_lag, no) || !disjoint(durations, nd, out_lag_inc, no) ||
         !disjoint(out_lag, no, out_lag_inc, no))
         return SF_EINVAL;
-    const bool vec2 = (R % 2 == 0) && aligned(durations, 16);
-    const LagVariant v = vec2 ? pick_lag<true, 2>(R) : pick_lag<true, 1>(R);
-    int Ri = R, Si = S;
-    void* args[] = {(void*)&durations, (void*)&T, (void*)&Ri, (void*)&Si, (void*)&out_lag,
-                    (void*)&out_lag_inc};
-    return launch_lag(v, T, args, stream);
+    return launch_lag<true>(durations, T, R, S, out_lag, out_lag_inc, stream);
 }
 
 SF_API int sf_rank_spread(const int64_t* durations, int64_t T, int32_t R, int32_t S,
@@ -682,13 +817,7 @@ SF_API int sf_rank_spread(const int64_t* durations, int64_t T, int32_t R, int32_
     if (!disjoint(durations, nd, out_spread, no) || !disjoint(durations, nd, out_window_spread, nw) ||
         !disjoint(out_spread, no, out_window_spread, nw))
         return SF_EINVAL;
-    const bool vec2 = (R % 2 == 0) && aligned(durations, 16);
-    const LagVariant v = vec2 ? pick_lag<false, 2>(R) : pick_lag<false, 1>(R);
-    int Ri = R, Si = S;
-    int64_t* unused = nullptr;
-    void* args[] = {(void*)&durations, (void*)&T, (void*)&Ri, (void*)&Si, (void*)&out_spread,
-                    (void*)&unused};
-    const int rc = launch_lag(v, T, args, stream);
+    const int rc = launch_lag<false>(durations, T, R, S, out_spread, nullptr, stream);
     if (rc != SF_OK) return rc;
     return launch_window_sum(out_spread, T, S, window, W, out_window_spread, stream);
 }

@@ -152,6 +152,40 @@ def test_selections_large_stage_counts(sf):
     np.testing.assert_array_equal(med.cpu().numpy(), oracle.window_median(d, 5))
 
 
+@pytest.mark.parametrize("R,S,T", [
+    (1, 5, 3), (2, 9, 5), (3, 40, 3), (127, 30, 9), (256, 17, 40), (257, 25, 1100), (511, 9, 4), (513, 40, 3),
+    (1023, 9, 5), (1025, 5, 6), (2047, 7, 3), (3001, 6, 700), (4095, 12, 2), (4097, 8, 3), (4098, 3, 430),
+    (8191, 5, 3), (8193, 4, 130), (16383, 4, 3), (16385, 3, 3), (16387, 2, 258), (24575, 2, 3), (24577, 3, 2),
+    (24576, 1, 257), (32767, 3, 2), (32769, 2, 2)])
+def test_lag_spread_shape_rules(sf, R, S, T):
+    """Both sides of every rule that picks a launch (steps split by stages,
+    rows for steps, the 32-bit shapes at any R), and what the copies of the
+    maximum in unused slots must not change: a median in the topmost bin, a
+    median that is the maximum, all values equal, one value far above; and
+    durations of 2^32 and more, which are handed over, in some of the steps."""
+    rng = np.random.Generator(np.random.PCG64(R * 17 + S))
+    d = rng.integers(0, 1000, size=(T, S, R), dtype=np.int64)
+    d[0::6] = 10**6 - d[0::6] // 990                       # most values at the top
+    d[1::6, :, :] = np.where(rng.random((len(d[1::6]), S, R)) < 0.6, 10**6, d[1::6])  # the median is the maximum
+    d[2::6] = 5
+    d[3::6, :, R // 2] += 10**8
+    d[4::6, S // 2, R - 1] += 1 << 33
+    if T > 8:
+        d[8:10] = (d[8:10] % 1000) << 31                   # neighbours handed over together
+    print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
+    flat = torch.zeros(T * S * R + 1, dtype=torch.int64, device=DEV)
+    view = flat[1:].view(T, S, R)
+    view.copy_(torch.from_numpy(d))
+    lag, inc = sf.sf_frontier_lag(view)
+    ol, oinc = oracle.frontier_lag(d)
+    np.testing.assert_array_equal(lag.cpu().numpy(), ol)
+    np.testing.assert_array_equal(inc.cpu().numpy(), oinc)
+    spread, win = sf.sf_rank_spread(view, 7)
+    osp, owin = oracle.rank_spread(d, 7)
+    np.testing.assert_array_equal(spread.cpu().numpy(), osp)
+    np.testing.assert_array_equal(win.cpu().numpy(), owin)
+
+
 @pytest.mark.parametrize("T", [1, 2, 3, 5, 15, 16, 17, 63, 65, 257])
 def test_frontier_ragged_steps(sf, T):
     for R in (8, 24, 128, 300):
