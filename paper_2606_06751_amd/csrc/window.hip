@@ -15,6 +15,8 @@
 #include "sf_host.h"
 #include "sf_select.h"
 
+#include <type_traits>
+
 namespace sfk {
 
 constexpr int kHistChunk = 16384;  // ranks per histogram workgroup (64 KB LDS)
@@ -158,18 +160,145 @@ __global__ __launch_bounds__(kTopWG) void k_window_top2(const int64_t* __restric
     }
 }
 
-// Fused frontier pass and window summary for small inputs (few ranks and
-// stages, short windows): one workgroup of 1024 threads per window does the
-// whole path of Sec. 3 for the window's steps.  Groups of G lanes own a step
-// (K ranks per lane, one rank tile, the packed keys and DPP maxima of
-// k_frontier), loading a chunk of stage rows at once; the group's last lane
-// writes each boundary's advance and leader as soon as the stage is reduced
-// and adds them into the window's LDS totals and lead counts; then the
-// workgroup writes the counts and picks the top-2.  One launch instead of
-// three, for callers bound by launch latency.
-constexpr int kFusedMaxR = 256;
-constexpr int kFusedMaxS = 64;
-constexpr int64_t kFusedMaxWindow = 1024;
+// A whole window in one workgroup: counts (or, WEIGHTED, the exposed time led),
+// stage totals and the top-2 from one read of its advances and leaders.  Bound
+// by latency: one launch instead of two, and every row read once, in order,
+// where the kernels above give each stage a workgroup that reads its column
+// of the rows.  Measured on MI355X, summary / time led: 128 ranks x 6 x 100000,
+// windows of 1000: 14.2 -> 5.7 / 14.9 -> 5.1 us; 500 x 12 x 40000, windows of
+// 2500: 15.4 -> 9.6 / 20.9 -> 9.8.  It takes windows whose table fits the LDS
+// of a CU and whose rows one workgroup reads in about the time of the other
+// kernels (a single window of 4000 x 12: 12.5 against 12.7 us), more of them
+// where several windows run at once.
+constexpr int kWholeWG = 1024;
+constexpr size_t kWholeLds = 144 * 1024;
+constexpr int64_t kWholeEntries = 32768;  // steps x stages of one window; twice that from four windows up
+
+static size_t whole_lds(int R, int S, size_t entry) { return (size_t)S * 8 + (size_t)S * R * entry; }
+static bool whole_fits(int64_t T, int R, int S, int64_t window, size_t entry)
+{
+    const int64_t n = window < T ? window : T;
+    const int64_t most = T / n >= 4 ? 2 * kWholeEntries : kWholeEntries;
+    return S <= kWholeWG && n <= most / S && (int64_t)S * R <= (int64_t)kWholeLds &&
+           whole_lds(R, S, entry) <= kWholeLds;
+}
+
+template <bool WEIGHTED>
+__global__ __launch_bounds__(kWholeWG) void k_window_whole(
+    const int64_t* __restrict__ inc, const int32_t* __restrict__ lead, int64_t T, int R, int S,
+    int64_t window, int64_t W, int64_t* __restrict__ exposed, int32_t* __restrict__ counts,
+    int64_t* __restrict__ lead_exposed, int32_t* __restrict__ top2)
+{
+    typedef typename std::conditional<WEIGHTED, u64, uint32_t>::type H;
+    extern __shared__ u64 wsh[];  // [S] totals, [S][R] table
+    u64* tot = wsh;
+    H* table = reinterpret_cast<H*>(wsh + S);
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int SR = S * R;
+    const int P = kWholeWG / S;  // steps read at once: a thread keeps to one stage
+    const int p = tid / S, s = tid - p * S;
+    for (int64_t w = blockIdx.x; w < W; w += gridDim.x) {
+        const int64_t t0 = w * window;
+        const int n = (int)(min(t0 + window, T) - t0);
+        for (int i = tid; i < S; i += kWholeWG) tot[i] = 0;
+        for (int i = tid; i < SR; i += kWholeWG) table[i] = 0;
+        __syncthreads();
+        if (p < P) {
+            u64 sum = 0;
+            const int64_t* iw = inc + t0 * S + s;
+            const int32_t* lw = lead + t0 * S + s;
+#pragma unroll 8
+            for (int t = p; t < n; t += P) {
+                const u64 a = (u64)iw[(int64_t)t * S];
+                const int r = lw[(int64_t)t * S];
+                sum += a;
+                if (r >= 0 && r < R) atomicAdd(&table[s * R + r], WEIGHTED ? (H)a : (H)1);
+            }
+            atomicAdd(&tot[s], sum);  // wraps as int64 sums do
+        }
+        __syncthreads();
+        if (WEIGHTED) {
+            for (int i = tid; i < SR; i += kWholeWG) lead_exposed[w * (int64_t)SR + i] = (int64_t)table[i];
+        } else {
+            for (int i = tid; i < S; i += kWholeWG) exposed[w * S + i] = (int64_t)tot[i];
+            for (int i = tid; i < SR; i += kWholeWG) counts[w * (int64_t)SR + i] = (int32_t)table[i];
+        }
+        if (tid < 128) {
+            // wave k takes pick k: the stages by total (a second maximum
+            // takes the lowest stage of equal ones), then its rank by table
+            // entry, the lowest rank of equal ones, where one is positive
+            const int k = __builtin_amdgcn_readfirstlane(tid >> 6);
+            auto lowest_max = [&](u64 key, int at) {  // key 0: none; the position, or -1
+                const u64 best = lane_value(group_max<64>(key), 63);
+                const u64 pos = best != 0 && key == best ? (u64)(0xFFFFFFFFu - (uint32_t)at) + 1ull : 0ull;
+                const u64 m = lane_value(group_max<64>(pos), 63);
+                return m ? (int)(0xFFFFFFFFu - (uint32_t)(m - 1ull)) : -1;
+            };
+            int pick = -1;
+            for (int j = 0; j <= k; ++j) {
+                u64 be = 0;
+                int bs = -1;
+                for (int i = lane; i < S; i += 64) {
+                    const u64 e = (tot[i] ^ 0x8000000000000000ull);
+                    if (i != pick && (bs < 0 || e > be)) {
+                        be = e;
+                        bs = i;
+                    }
+                }
+                // (a total of INT64_MIN has key 0: one more tells it from none)
+                const u64 top = lane_value(group_max<64>(bs < 0 ? 0ull : be), 63);
+                pick = lowest_max(bs >= 0 && be == top ? 1ull : 0ull, bs);
+            }
+            int rank = -1;
+            if (pick >= 0) {
+                u64 bv = 0;
+                int br = -1;
+                for (int r = lane; r < R; r += 64) {
+                    const H v = table[pick * R + r];
+                    const u64 x = WEIGHTED && (int64_t)v < 0 ? 0ull : (u64)v;
+                    if (x > bv) {
+                        bv = x;
+                        br = r;
+                    }
+                }
+                rank = lowest_max(bv, br);
+            }
+            if (lane == 0) {
+                top2[w * 4 + 2 * k] = pick;
+                top2[w * 4 + 2 * k + 1] = rank;
+            }
+        }
+        __syncthreads();  // the tables are cleared for the next window
+    }
+}
+
+template <bool WEIGHTED>
+static int launch_whole(const int64_t* inc, const int32_t* lead, int64_t T, int R, int S, int64_t window, int64_t W,
+                        int64_t* exposed, int32_t* counts, int64_t* lead_exposed, int32_t* top2, sf_stream_t stream)
+{
+    void* args[] = {(void*)&inc, (void*)&lead, (void*)&T, (void*)&R, (void*)&S, (void*)&window, (void*)&W,
+                    (void*)&exposed, (void*)&counts, (void*)&lead_exposed, (void*)&top2};
+    return launch(reinterpret_cast<const void*>(&k_window_whole<WEIGHTED>), dim3((unsigned)(W < 65536 ? W : 65536)),
+                  dim3(kWholeWG), args, whole_lds(R, S, WEIGHTED ? 8 : 4), stream);
+}
+
+// Fused frontier pass and window summary for the smallest inputs: one
+// workgroup of 1024 threads per window does the whole path of Sec. 3 for the
+// window's steps.  Groups of G lanes own a step (K ranks per lane, one rank
+// tile, the packed keys and DPP maxima of k_frontier), loading a chunk of
+// stage rows at once; the group's last lane writes each boundary's advance and
+// leader as soon as the stage is reduced and adds them into the window's LDS
+// totals and lead counts; then the workgroup writes the counts and picks the
+// top-2.  One launch instead of two, where the workgroup takes the window in
+// one round of 256 steps with every row in flight at once (8 ranks x 6 x 1000,
+// windows of 100: 6.1 against 7.1 us).  A second round or chunk of rows costs
+// a memory latency in series and leaves the other CUs idle: windows of 1000 of
+// the same 17.7 against 8.4 us, 15 ranks 8.0 against 7.1, 256 ranks x 6 x 300
+// 63.8 against 9.0.
+constexpr int kFusedMaxR = 8;
+constexpr int kFusedMaxS = 8;
+constexpr int64_t kFusedMaxWindow = 256;
 constexpr int64_t kFusedMaxSamples = 1 << 20;
 
 constexpr int kFusedWG = 1024;  // threads of the fused kernel: 1024 / G steps per round
@@ -203,7 +332,7 @@ __global__ __launch_bounds__(kFusedWG) void k_frontier_summary(
     static_assert(K % VEC == 0 && G <= 32, "one DPP group per step");
     constexpr int SPW = kFusedWG / G;  // steps per round
     constexpr int NLD = K / VEC;
-    constexpr int CH = K >= 8 ? 1 : 16 / K;  // stage rows loaded at once (up to 16 values per lane)
+    constexpr int CH = 16 / K;  // stage rows loaded at once
     __shared__ u64 ex_sh[kFusedMaxS];
     __shared__ int32_t cnt_sh[kFusedMaxS * kFusedMaxR];
     const int tid = threadIdx.x;
@@ -293,9 +422,9 @@ __global__ __launch_bounds__(kFusedWG) void k_frontier_summary(
         if (tid < 64) {
             // wave 0 alone picks the top-2 with DPP wave maxima (no block
             // barriers): the stage of the largest total (a second max takes
-            // the lowest stage among the lanes holding it; S <= 64, one stage
-            // per lane), then its most frequent leader (R <= 256, four ranks
-            // per lane, the lowest rank on equal counts)
+            // the lowest stage among the lanes holding it, one stage per
+            // lane), then its most frequent leader (the lowest rank on equal
+            // counts)
             const int lane = tid;
             int sk = -1;
             for (int k = 0; k < 2; ++k) {
@@ -322,17 +451,6 @@ __global__ __launch_bounds__(kFusedWG) void k_frontier_summary(
         }
         __syncthreads();  // the LDS tables are cleared for the next window
     }
-}
-
-template <int VEC>
-const void* pick_fused(int R)
-{
-    if (R <= 8) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 4>);
-    if (R <= 16) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 8>);
-    if (R <= 32) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 16>);
-    if (R <= 64) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 32>);
-    if (R <= 128) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 4, 32>);
-    return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 8, 32>);  // R <= kFusedMaxR
 }
 
 // Exposed time led: the same segmented histogram as k_window_counts, with
@@ -616,6 +734,9 @@ SF_API int sf_window_summary(const int64_t* increment, const int32_t* leader, in
         for (int b = (a < 2 ? 2 : a + 1); b < 5; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
 
+    if (whole_fits(T, R, S, window, 4))
+        return launch_whole<false>(increment, leader, T, R, S, window, W, out_stage_exposed, out_lead_counts,
+                                   nullptr, out_top2, stream);
     const int nchunk = (R + kHistChunk - 1) / kHistChunk;
     const int64_t items = W * S * nchunk;
     const unsigned g1 = (unsigned)(items < 1048576 ? items : 1048576);
@@ -654,6 +775,9 @@ SF_API int sf_window_lead_exposed(const int64_t* increment, const int32_t* leade
         for (int b = (a < 2 ? 2 : a + 1); b < 4; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
 
+    if (whole_fits(T, R, S, window, 8))
+        return launch_whole<true>(increment, leader, T, R, S, window, W, nullptr, nullptr, out_lead_exposed,
+                                  out_top2, stream);
     const int nchunk = (R + kLeadChunk - 1) / kLeadChunk;
     const int64_t items = W * S * nchunk;
     const unsigned g1 = (unsigned)(items < 1048576 ? items : 1048576);
@@ -727,7 +851,8 @@ SF_API int sf_frontier_summary(const int64_t* durations, int64_t T, int32_t R, i
     if (R <= kFusedMaxR && S <= kFusedMaxS && n_max <= kFusedMaxWindow &&
         T * S * (int64_t)R <= kFusedMaxSamples) {
         const bool vec2 = (R % 2 == 0) && aligned(durations, 16);
-        const void* fn = vec2 ? pick_fused<2>(R) : pick_fused<1>(R);
+        const void* fn = vec2 ? reinterpret_cast<const void*>(&k_frontier_summary<2, 2, 4>)
+                              : reinterpret_cast<const void*>(&k_frontier_summary<1, 2, 4>);
         int Ri = R, Si = S;
         int64_t Wl = W;
         void* args[] = {(void*)&durations,         (void*)&T,               (void*)&Ri,

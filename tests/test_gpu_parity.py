@@ -411,6 +411,33 @@ def test_lead_exposed_from_oracle_steps(sf, R, S, T, window):
     assert_lead_exposed_equal(sf, inc, lead, R, window)
 
 
+@pytest.mark.parametrize("R,S,T,window", [
+    (1, 1, 5, 3), (3, 1, 2000, 1000), (7, 8, 600, 256), (8, 9, 600, 256), (9, 8, 300, 100), (8, 8, 900, 257),
+    (64, 64, 515, 512), (64, 64, 514, 513), (20, 1024, 70, 32), (20, 1025, 70, 32), (16, 70, 1500, 468),
+    (1023, 8, 40, 7), (2300, 8, 40, 7), (2303, 8, 40, 19), (2303, 16, 40, 19), (2305, 16, 40, 19), (36000, 1, 90, 30)])
+def test_window_whole_edges(sf, R, S, T, window):
+    """Both sides of the rules that give a whole window to one workgroup (its
+    table in LDS, its steps x stages) and of the fused call's limits: leaders
+    outside [0, R) and ties of counts, totals and led time, negative advances
+    (a rank with a negative sum leads nothing) and totals of INT64_MIN."""
+    rng = np.random.Generator(np.random.PCG64(R * 13 + S))
+    inc = rng.integers(-3, 6, size=(T, S), dtype=np.int64)
+    lead = rng.integers(-1, R + 1, size=(T, S), dtype=np.int32)
+    lead[::2] = rng.integers(0, min(R, 3), size=lead[::2].shape)
+    inc[:window, S // 2:] = 0
+    inc[0, 0] = -(1 << 63) if T > window else 5
+    inc[1:window, 0] = 0
+    inc[-1, :] = 10**15
+    print("case R=%d S=%d T=%d window=%d" % (R, S, T, window), flush=True)
+    assert_summary_equal(sf, inc, lead, R, window)
+    assert_lead_exposed_equal(sf, inc, lead, R, window)
+    d = rng.integers(0, 1000, size=(T, S, R), dtype=np.int64)
+    out = sf.sf_frontier_summary(torch.from_numpy(d).to(DEV), window)
+    oi, ol = oracle.frontier(d)
+    for g, o in zip(out, (oi, ol) + tuple(oracle.window_summary(oi, ol, R, window))):
+        np.testing.assert_array_equal(g.cpu().numpy(), o)
+
+
 def test_lead_exposed_ties_signs_and_out_of_range_leaders(sf):
     """Stage-total ties, rank ties on exposed time, zero rows (rank -1),
     negative advances (never a suspect) and leaders outside [0, R)."""
