@@ -74,7 +74,10 @@ __device__ __forceinline__ void ev_store(int64_t i, const EvAcc& a, u64 kprev, i
 // Same step/lane layout as k_frontier: G lanes per step, K ranks per lane,
 // WG / G steps per workgroup.  When one group of at most 64 lanes covers all
 // R ranks of its step, the group's last lane writes each boundary's outputs
-// as soon as the stage is reduced; otherwise partial results go through LDS
+// as soon as the stage is reduced (groups of up to 16 lanes: G boundaries at a
+// time, a lane each; one lane's 8-byte stores leave the L2 partly filled lines
+// of more steps than it holds: 16 ranks x 74 x 75909 668 -> 232 us);
+// otherwise partial results go through LDS
 // (5 arrays of [WG / min(G, 64)][S]) and the workgroup writes them at the end.
 // GTAB (stage counts past what LDS holds; G <= 64): the group's last lane
 // keeps the partial results of its step in the step's own output rows (the
@@ -82,12 +85,20 @@ __device__ __forceinline__ void ev_store(int64_t i, const EvAcc& a, u64 kprev, i
 // max and sum in their final rows), and after the last tile the workgroup
 // decodes the increment, leader and gap in place, chunk by chunk from the
 // end, each chunk read before any of it is written.
-template <int VEC, int K, int G, int WG, bool GTAB>
+//
+// The ranks are loaded in pairs, 16 bytes at any 8-byte alignment (V: 1 where
+// R == 1, 2 for even R, 3 for odd).  Slots past R, and at odd R the first slot of the last pair
+// (it overlaps the pair before), load ranks that other slots hold: their
+// duration counts as 0 and their key stays 0, below every real key.
+// D: stage rows in flight (as in k_frontier).
+template <int V, int K, int G, int WG, bool GTAB, int D>
 __global__ __launch_bounds__(WG) void k_frontier_evidence(
     const int64_t* __restrict__ d, int64_t T, int R, int S, int64_t* __restrict__ inc,
     int32_t* __restrict__ lead, int64_t* __restrict__ gap, int32_t* __restrict__ ties,
     int64_t* __restrict__ stage_max, int64_t* __restrict__ stage_sum)
 {
+    constexpr int VEC = V == 1 ? 1 : 2;
+    constexpr bool ODD = V == 3;
     static_assert(K % VEC == 0 && (WG % G == 0 || G == WG), "shape");
     static_assert(!GTAB || G <= 64, "GTAB: one writer lane per step");
     constexpr int SUB = G < 64 ? G : 64;
@@ -110,40 +121,46 @@ __global__ __launch_bounds__(WG) void k_frontier_evidence(
     const int slot = tid / SUB;
     const bool writer = (tid % SUB) == SUB - 1;
     const int64_t tb = xcd_block() * SPW;
-    const int64_t t = tb + tid / G;
+    // wave-uniform where a wave holds one step: the row base in SGPRs
+    const int64_t t = tb + (G >= 64 ? __builtin_amdgcn_readfirstlane(tid / G) : tid / G);
 
     if (t < T) {  // uniform over the step group
         const int64_t* dt = d + t * (int64_t)S * R;
         for (int r0 = 0; r0 < R; r0 += RT) {
+            // (a tile of one rank starts one below it)
+            const int rb = r0 < R - VEC ? r0 : R - VEC;
+            const int last = R - VEC - rb;  // the last pair's place in the tile
             u64 q[K];
-            bool ok[NLD];
+            bool ok[NLD], ok0[NLD];  // the pair's second (or only), first slot holds a rank
 #pragma unroll
             for (int l = 0; l < NLD; ++l) {
                 const int r = r0 + (l * G + gl) * VEC;
                 ok[l] = r < R;
+                ok0[l] = ODD ? r <= R - VEC : ok[l];
 #pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                    q[l * VEC + e] = ok[l] ? (kRankMask - (u64)(r + e)) : 0ull;
+                for (int e = 0; e < VEC; ++e) {
+                    const int at = ok0[l] ? r + e : R - VEC + e;
+                    q[l * VEC + e] = (ODD && e == 0 ? ok0[l] : ok[l]) ? (kRankMask - (u64)at) : 0ull;
+                }
             }
-            int64_t v[K];
-            auto load_row = [&](int s) {
-                const int64_t* row = dt + (int64_t)s * R + r0;
+            int64_t v[D][K];
+            auto load_row = [&](int c, int s) {
+                const int64_t* row = dt + (int64_t)s * R + rb;
 #pragma unroll
                 for (int l = 0; l < NLD; ++l) {
-                    const int idx = ok[l] ? (l * G + gl) * VEC : 0;
+                    const uint32_t idx = (uint32_t)(ok0[l] ? (l * G + gl) * VEC : last);
                     if (VEC == 2) {
-                        const v2i64 x = __builtin_nontemporal_load(reinterpret_cast<const v2i64*>(row + idx));
-                        v[2 * l] = x.x;
-                        v[2 * l + 1] = x.y;
+                        const v2i64_a8 x = __builtin_nontemporal_load(reinterpret_cast<const v2i64_a8*>(row + idx));
+                        v[c][2 * l] = x.x;
+                        v[c][2 * l + 1] = x.y;
                     } else {
-                        v[l] = __builtin_nontemporal_load(row + idx);
+                        v[c][l] = __builtin_nontemporal_load(row + idx);
                     }
                 }
             };
-            load_row(0);
-            u64 kprev = 0;
-            for (int s = 0; s < S; ++s) {
-                EvAcc a;
+            u64 kprev = 0, hprev = 0;
+            EvAcc a, held = {};
+            auto advance = [&](int c) {
                 a.k1 = 0;
                 a.k2 = 0;
                 a.smax = 0;
@@ -151,9 +168,7 @@ __global__ __launch_bounds__(WG) void k_frontier_evidence(
                 a.c = 0;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    // slots past R carry no rank: their duration counts as 0
-                    // and their key stays 0, below every real key
-                    const int64_t dv = ok[k / VEC] ? v[k] : 0;
+                    const int64_t dv = (ODD && k % 2 == 0 ? ok0[k / VEC] : ok[k / VEC]) ? v[c][k] : 0;
                     q[k] += (u64)dv << kRankBits;
                     a.k2 = umax64(a.k2, umin64(a.k1, q[k]));
                     a.k1 = umax64(a.k1, q[k]);
@@ -162,10 +177,22 @@ __global__ __launch_bounds__(WG) void k_frontier_evidence(
                 }
 #pragma unroll
                 for (int k = 0; k < K; ++k)
-                    a.c += (ok[k / VEC] && ((q[k] ^ a.k1) >> kRankBits) == 0) ? 1u : 0u;
-                if (s + 1 < S) load_row(s + 1);
+                    a.c += ((ODD && k % 2 == 0 ? ok0[k / VEC] : ok[k / VEC]) && ((q[k] ^ a.k1) >> kRankBits) == 0) ? 1u : 0u;
+            };
+            auto reduce = [&](int s) {
                 a = ev_group_reduce<SUB>(a);
-                if (writer) {
+                if (G <= 16 && direct) {
+                    // every lane has the result: lane s % G keeps it, and G
+                    // boundaries are written at once
+                    const int own = s % G;
+                    if (gl == own) {
+                        held = a;
+                        hprev = kprev;
+                    }
+                    kprev = a.k1;
+                    if ((own == G - 1 || s == S - 1) && gl <= own)
+                        ev_store(t * S + s - own + gl, held, hprev, R, inc, lead, gap, ties, stage_max, stage_sum);
+                } else if (writer) {
                     if (direct) {
                         ev_store(t * S + s, a, kprev, R, inc, lead, gap, ties, stage_max, stage_sum);
                         kprev = a.k1;
@@ -203,6 +230,37 @@ __global__ __launch_bounds__(WG) void k_frontier_evidence(
                         t_c[i] = a.c;
                         t_max[i] = (u64)a.smax;
                         t_sum[i] = (u64)a.ssum;
+                    }
+                }
+            };
+            if constexpr (D == 1) {
+                load_row(0, 0);
+                for (int s = 0; s < S; ++s) {
+                    advance(0);
+                    if (s + 1 < S) load_row(0, s + 1);
+                    reduce(s);
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < D; ++c)
+                    if (c < S) load_row(c, c);
+                int s = 0;
+                for (; s + 2 * D <= S; s += D) {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        advance(c);
+                        load_row(c, s + c + D);
+                        reduce(s + c);
+                    }
+                }
+                for (; s < S; s += D) {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        if (s + c < S) {
+                            advance(c);
+                            if (s + c + D < S) load_row(c, s + c + D);
+                            reduce(s + c);
+                        }
                     }
                 }
             }
@@ -252,7 +310,7 @@ __global__ __launch_bounds__(WG) void k_frontier_evidence(
         a.smax = (int64_t)t_max[i0];
         a.ssum = (int64_t)t_sum[i0];
         u64 kp = s > 0 ? t_k1[i0 - 1] : 0;
-#pragma unroll
+#pragma unroll(SPS <= 4 ? SPS : 2)
         for (int qd = 1; qd < SPS; ++qd) {
             const int iq = (jj * SPS + qd) * S + s;
             p.k1 = t_k1[iq];
@@ -273,10 +331,10 @@ struct EvidenceVariant {
     int per_cu;  // resident workgroups per CU to allow (0: no cap)
 };
 
-template <int VEC, int K, int G, int WG, bool GTAB = false>
+template <int V, int K, int G, int WG, bool GTAB = false, int D = 1>
 EvidenceVariant ev_variant(int per_cu)
 {
-    return EvidenceVariant{reinterpret_cast<const void*>(&k_frontier_evidence<VEC, K, G, WG, GTAB>),
+    return EvidenceVariant{reinterpret_cast<const void*>(&k_frontier_evidence<V, K, G, WG, GTAB, D>),
                            K, G, WG, per_cu};
 }
 
@@ -290,39 +348,82 @@ size_t ev_lds_need(const EvidenceVariant& v, int R, int S, bool gtab)
     return (size_t)5 * (v.WG / sub) * S * 8;
 }
 
-// Launch shape by rank count, measured on MI355X; a shape whose LDS would
-// exceed 64 KB at this S falls back to two 64-lane slots per step
-// (80 * S bytes, at most 40 KB).
-template <int VEC>
-EvidenceVariant pick_evidence(int R, int S)
+// Few steps (measured on MI355X): a wave or more per step and four rows in
+// flight, where the shapes below leave the chip idle, up to 1 MB (256 ranks: 2
+// MB) of stage rows over all steps (1023 x 8 x 128 26 -> 12 us, 130 x 60 x 128
+// 120 -> 41; at 8 MB 27 -> 36); past 8192 ranks all 1024 lanes.  From 1025 to
+// 8192 ranks the reductions of so many waves cost more than they hide.
+static bool ev_deep(int64_t T, int R)
 {
+    const int64_t row = T * R * 8;
+    if (R > 8192) return T < 400;
+    return R > 64 && R <= 1024 && row <= (R <= 256 ? 2 << 20 : 1 << 20);
+}
+
+template <int V>
+EvidenceVariant pick_evidence_deep(int R)
+{
+    if (R <= 128) return ev_variant<V, 2, 64, 64, false, 4>(0);
+    if (R <= 256) return ev_variant<V, 2, 128, 128, false, 4>(0);
+    if (R <= 512) return ev_variant<V, 2, 256, 256, false, 4>(0);
+    if (R <= 1024) return ev_variant<V, 2, 512, 512, false, 4>(0);
+    return ev_variant<V, 16, 1024, 1024>(0);
+}
+
+// Launch shape by rank count, measured on MI355X: the pass is bound by its VALU
+// work as much as by HBM (about 20 instructions per slot, ranks or not), so
+// the tile is close to R, and its groups are as few lanes as hold it at 12 to
+// 16 ranks each, since a reduction costs as much as 8 to 10 slots (1500 x 10
+// x 8192: 356 -> 164 us, 671 x 8 x 8192 85 -> 63, 1024 x 12 x 8192 149 -> 128,
+// 6001 x 10 x 1024 133 -> 84; 250 ranks on 32 lanes level, 256 110 against
+// 115; 8192 ranks at 16 each, 32 MB of rows and more, 126 against 130).  A
+// shape whose LDS would exceed 64 KB at this S falls back to two 64-lane slots per step
+// (80 * S bytes, at most 40 KB).
+template <int V>
+EvidenceVariant pick_evidence(int64_t T, int R, int S)
+{
+    if (ev_deep(T, R)) {
+        const EvidenceVariant v = pick_evidence_deep<V>(R);
+        if (ev_lds_need(v, R, S, false) <= kLdsMaxPerWg) return v;
+    }
     EvidenceVariant v;
-    if (R <= 8) v = ev_variant<VEC, 2, 4, 64>(0);
-    else if (R <= 16) v = ev_variant<VEC, 2, 8, 64>(0);
-    else if (R <= 32) v = ev_variant<VEC, 4, 8, 64>(0);
-    else if (R <= 64) v = ev_variant<VEC, 4, 16, 64>(0);
-    else if (R <= 128) v = ev_variant<VEC, 8, 16, 256>(8);
-    else if (R <= 256) v = ev_variant<VEC, 8, 16, 256>(8);
-    else if (R <= 512) v = ev_variant<VEC, 16, 32, 64>(0);
-    else if (R <= 1024) v = ev_variant<VEC, 16, 32, 64>(8);
-    else if (R <= 4096) v = ev_variant<VEC, 16, 256, 256>(2);
-    else v = ev_variant<VEC, 32, 256, 256>(0);
-    if (ev_lds_need(v, R, S, false) > kLdsMaxPerWg) v = ev_variant<VEC, 16, 128, 128>(0);
+    if (R == 1) v = ev_variant<1, 2, 4, 64>(0);
+    else if (R <= 8) v = ev_variant<V, 2, 4, 64, false, 4>(0);
+    else if (R <= 16) v = ev_variant<V, 2, 8, 64, false, 4>(0);
+    else if (R <= 32) v = ev_variant<V, 4, 8, 64>(0);
+    else if (R <= 64) v = ev_variant<V, 4, 16, 64>(0);
+    else if (R <= 128) v = ev_variant<V, 8, 16, 256>(8);
+    else if (R <= 240) v = ev_variant<V, 8, 32, 64>(0);
+    else if (R <= 256) v = ev_variant<V, 8, 16, 256>(8);
+    else if (R <= 384) v = ev_variant<V, 12, 32, 64>(0);
+    else if (R <= 512) v = ev_variant<V, 16, 32, 64>(0);
+    else if (R <= 768) v = ev_variant<V, 12, 64, 64>(0);
+    else if (R <= 1024) v = ev_variant<V, 16, 64, 64>(0);
+    else if (R <= 1536) v = ev_variant<V, 12, 128, 128>(0);
+    else if (R <= 2048) v = ev_variant<V, 16, 128, 128>(0);
+    else if (R <= 3072) v = ev_variant<V, 12, 256, 256>(2);
+    else if (R <= 4096) v = ev_variant<V, 16, 256, 256>(2);
+    else if (R <= 6144) v = ev_variant<V, 12, 512, 512>(0);
+    else if (R <= 8192 && T < 400) v = ev_variant<V, 16, 512, 512>(0);
+    else if (R > 8192 && R <= 12288) v = ev_variant<V, 24, 512, 512>(0);
+    else v = ev_variant<V, 32, 256, 256>(0);
+    if (ev_lds_need(v, R, S, false) > kLdsMaxPerWg) v = ev_variant<V, 16, 128, 128>(0);
     return v;
 }
 
 // Stage counts whose LDS table would not fit even the two-slot fallback
 // (more than 819 stages): one group of at most 64 lanes per step, the
 // partial results in the output rows.
-template <int VEC>
+template <int V>
 EvidenceVariant pick_evidence_gtab(int R)
 {
-    if (R <= 8) return ev_variant<VEC, 2, 4, 64, true>(0);
-    if (R <= 16) return ev_variant<VEC, 2, 8, 64, true>(0);
-    if (R <= 32) return ev_variant<VEC, 4, 8, 64, true>(0);
-    if (R <= 64) return ev_variant<VEC, 4, 16, 64, true>(0);
-    if (R <= 512) return ev_variant<VEC, 16, 32, 64, true>(0);
-    return ev_variant<VEC, 16, 64, 64, true>(0);
+    if (R == 1) return ev_variant<1, 2, 4, 64, true>(0);
+    if (R <= 8) return ev_variant<V, 2, 4, 64, true>(0);
+    if (R <= 16) return ev_variant<V, 2, 8, 64, true>(0);
+    if (R <= 32) return ev_variant<V, 4, 8, 64, true>(0);
+    if (R <= 64) return ev_variant<V, 4, 16, 64, true>(0);
+    if (R <= 512) return ev_variant<V, 16, 32, 64, true>(0);
+    return ev_variant<V, 16, 64, 64, true>(0);
 }
 
 }  // namespace sfk
@@ -349,10 +450,10 @@ SF_API int sf_frontier_evidence(const int64_t* durations, int64_t T, int32_t R, 
         for (int b = (a < 1 ? 1 : a + 1); b < 7; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
 
-    const bool vec2 = (R % 2 == 0) && aligned(durations, 16);
-    EvidenceVariant v = vec2 ? pick_evidence<2>(R, S) : pick_evidence<1>(R, S);
+    const bool odd = R & 1;
+    EvidenceVariant v = odd ? pick_evidence<3>(T, R, S) : pick_evidence<2>(T, R, S);
     const bool gtab = ev_lds_need(v, R, S, false) > kLdsMaxPerWg;
-    if (gtab) v = vec2 ? pick_evidence_gtab<2>(R) : pick_evidence_gtab<1>(R);
+    if (gtab) v = odd ? pick_evidence_gtab<3>(R) : pick_evidence_gtab<2>(R);
     const int spw = v.WG / v.G;
     const size_t lds = lds_request(ev_lds_need(v, R, S, gtab), v.per_cu);
     const int64_t blocks = (T + spw - 1) / spw;

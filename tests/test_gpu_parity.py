@@ -153,6 +153,32 @@ def test_selections_large_stage_counts(sf):
 
 
 @pytest.mark.parametrize("R,S,T", [
+    (1, 7, 9), (2, 9, 5), (3, 17, 70), (8, 33, 9), (15, 5, 40), (17, 16, 3), (31, 40, 9), (63, 15, 20), (65, 6, 5),
+    (127, 9, 2100), (129, 5, 3), (241, 5, 1100), (255, 6, 1100), (257, 4, 600), (385, 3, 400), (511, 5, 9),
+    (513, 6, 300), (769, 4, 200), (1023, 5, 9), (1025, 5, 5), (1535, 3, 4), (1537, 3, 4), (2047, 7, 3), (2049, 4, 3),
+    (3073, 4, 3), (4097, 4, 3), (6145, 3, 3), (6145, 2, 401), (8191, 5, 2), (8193, 3, 3), (8193, 2, 401), (12289, 2, 3),
+    (16385, 3, 2), (32769, 2, 2), (1023, 140, 2), (129, 200, 2)])
+def test_evidence_shape_rules(sf, R, S, T):
+    """Both sides of every rule that picks a launch shape of the evidence pass:
+    odd rank counts (the first slot of the overlapping last pair must not count
+    twice), a tile of one rank, stage counts around the boundaries that a group
+    writes at once and the rows in flight, an LDS table too large for the deep
+    shape; ties with the last rank, and a last rank alone in front."""
+    rng = np.random.Generator(np.random.PCG64(R * 7 + S))
+    d = rng.integers(0, 1000, size=(T, S, R), dtype=np.int64)
+    d[0::3, S // 2, R - 1] += 10**6
+    d[1::3, 0, max(R - 2, 0):] = 10**6
+    d[2::6] = 7
+    flat = torch.zeros(T * S * R + 1, dtype=torch.int64, device=DEV)
+    view = flat[1:].view(T, S, R)
+    view.copy_(torch.from_numpy(d))
+    print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
+    ev, want = sf.sf_frontier_evidence(view), oracle.frontier_evidence(d)
+    for gk, ok in EV_KEYS.items():
+        np.testing.assert_array_equal(ev[gk].cpu().numpy(), want[ok], err_msg=gk)
+
+
+@pytest.mark.parametrize("R,S,T", [
     (1, 5, 3), (2, 9, 5), (3, 40, 3), (127, 30, 9), (256, 17, 40), (257, 25, 1100), (511, 9, 4), (513, 40, 3),
     (1023, 9, 5), (1025, 5, 6), (2047, 7, 3), (3001, 6, 700), (4095, 12, 2), (4097, 8, 3), (4098, 3, 430),
     (8191, 5, 3), (8193, 4, 130), (16383, 4, 3), (16385, 3, 3), (16387, 2, 258), (24575, 2, 3), (24577, 3, 2),
