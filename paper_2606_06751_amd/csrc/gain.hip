@@ -673,9 +673,8 @@ SF_API int sf_exposure_gain(const int64_t* durations, const int64_t* baseline, i
     const int spw = v.WG / v.G;
     const int64_t blocks = (T + spw - 1) / spw;
     if (blocks > INT32_MAX) return SF_EINVAL;
-    int rc = launch(v.fn, dim3((unsigned)blocks), dim3(v.WG), args, lds, stream);
+    const int rc = launch(v.fn, dim3((unsigned)blocks), dim3(v.WG), args, lds, stream);
     if (rc != SF_OK) return rc;
-    rc = launch_window_sum(out_gain, T, S, window, W, out_window_gain, stream);
-    if (rc != SF_OK) return rc;
-    return launch_window_sum(out_makespan, T, 1, window, W, out_window_makespan, stream);
+    return launch_window_sum(out_gain, T, S, window, W, out_window_gain, out_makespan,
+                             out_window_makespan, stream);
 }

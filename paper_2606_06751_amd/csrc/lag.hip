@@ -819,5 +819,5 @@ SF_API int sf_rank_spread(const int64_t* durations, int64_t T, int32_t R, int32_
         return SF_EINVAL;
     const int rc = launch_lag<false>(durations, T, R, S, out_spread, nullptr, stream);
     if (rc != SF_OK) return rc;
-    return launch_window_sum(out_spread, T, S, window, W, out_window_spread, stream);
+    return launch_window_sum(out_spread, T, S, window, W, out_window_spread, nullptr, nullptr, stream);
 }

@@ -58,9 +58,9 @@ static inline int device_cus(sf_stream_t stream, int* cus)
     return SF_OK;
 }
 
-// Window sums of the columns of a [T][C] int64 array into [W][C]
-// (window.hip).
+// Window sums of the columns of a [T][C] int64 array into [W][C] and, where y
+// is given, of a [T] array into [W], in one launch (window.hip).
 int launch_window_sum(const int64_t* x, int64_t T, int C, int64_t window, int64_t W,
-                      int64_t* out, sf_stream_t stream);
+                      int64_t* out, const int64_t* y, int64_t* out_y, sf_stream_t stream);
 
 }  // namespace sfk
