@@ -21,6 +21,7 @@
 #include "sf_host.h"
 #include "sf_select.h"
 
+#include <numeric>
 #include <type_traits>
 
 namespace sfk {
@@ -93,10 +94,14 @@ __device__ __forceinline__ int held_first_bin(uint32_t u, int lo) { return (int)
 // twice the workgroups per CU, which cover each other's barriers.  The stage's loads are consumed in
 // chunks so that few hold registers at once.  A step where a duration or a
 // rebased prefix reaches 2^32 (detected on the load, by the high word or the
-// carry of the 32-bit add) is handed over: once the step is done, its
+// carry of the 32-bit add) is handed over: its loads and selects stop, and its
 // out[t][0] is set to kRedo; a second launch of the 64-bit kernel with REDO
-// recomputes exactly those steps (every other workgroup of it returns at
-// once).  Both compute the same lower median of the same values.
+// recomputes exactly those steps.  Both compute the same lower median of the
+// same values.  With one stage of 6 s in every step, 32-bit pass and hand-over
+// against a 64-bit pass alone: the lag of 12289 ranks x 9 x 500 153 : 148 us, of
+// 5000 x 9 x 4000 417 : 375; the raw spread of 1023 x 8 x 4000 60 : 77, of 3000 x 8
+// x 4000 191 : 179 (without such stages 303 : 372 us for 5000 x 9 x 4000, 142 :
+// 237 for 3001 x 8 x 4000).
 constexpr int64_t kRedo = INT64_MIN;  // outputs are >= 0 under the data contract
 
 //
@@ -117,7 +122,38 @@ constexpr int64_t kRedo = INT64_MIN;  // outputs are >= 0 under the data contrac
 // first once more for the increment.  A boundary costs 2 to 3 us in series
 // (LDS latency and barriers), its durations a re-read from the caches: 429
 // ranks x 220 stages x 128 steps 616 -> 222 us.
-constexpr int kRedoRows = 8;  // steps whose markers one workgroup of the REDO launch looks at
+
+// Steps per workgroup (SC) of the REDO launch.  One workgroup for each of 10000
+// steps costs 14 us where none is marked (about 1 ns per workgroup and up), but
+// the marked steps of one workgroup follow each other: with every step marked,
+// eight each left the chip idle below 2000 steps of 16 waves (16384 ranks x 12 x
+// 256: 802 us against 202).  So there are as many workgroups as run at once (at
+// 128 VGPRs; the streaming kernel takes half of that), four times as many
+// where that is below kRedoGroups, and a workgroup looks at up to kRedoRows steps.
+// They lie a whole grid apart, so a stretch of marked steps is shared out, and
+// where the steps are the rows of several stages, the grid has no factor in
+// common with the stages: one long stage is not one workgroup's every time.
+constexpr int kRedoRows = 8;
+constexpr int64_t kRedoWaves = 4096;   // resident on the chip
+constexpr int64_t kRedoGroups = 4096;  // at least the workgroups of one wave that are
+
+struct RedoGrid {
+    int64_t blocks;
+    int rows;
+};
+
+// T steps (rows of `stages` stages where that is above 1)
+static RedoGrid redo_grid(int64_t T, int waves, bool streaming, int stages)
+{
+    const int64_t at_once = (streaming ? 2 : 1) * kRedoWaves / waves;
+    const int64_t most = at_once * 4 < kRedoGroups ? at_once * 4 : kRedoGroups;
+    const int64_t rounds = (T + most * kRedoRows - 1) / (most * kRedoRows);
+    RedoGrid g;
+    g.rows = (int)((T + most * rounds - 1) / (most * rounds));
+    g.blocks = (T + g.rows - 1) / g.rows;
+    while (g.rows > 1 && std::gcd(g.blocks, (int64_t)stages) != 1) ++g.blocks;
+    return g;
+}
 
 template <bool PREFIX, int VEC, int K, int WG, int LCAP, bool PUBU, bool FULL, bool NARROW,
           bool REDO, bool SPLIT>
@@ -132,6 +168,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
     constexpr int NW = WG / 64;
     constexpr int NLD = NARROW ? K / 2 : K / VEC;
     constexpr bool ODD = NARROW && VEC == 1;  // odd R: the narrow pass loads pairs all the same
+    constexpr bool AHEAD = !NARROW && (PREFIX || !REDO);  // the next stage's rows loaded a stage ahead
     constexpr bool SCAN_ALL = !PREFIX && NW > 1;
     constexpr int NH = SCAN_ALL ? 3 : 2;  // histograms
     // per-wave max/min partials, double-buffered by stage parity: a wave
@@ -159,19 +196,31 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
     }
     uint32_t todo = 0;  // REDO: the steps of this workgroup that the narrow pass handed over
     if (REDO) {
-        unit = (int64_t)blockIdx.x * kRedoRows;
-        todo = (uint32_t)__ballot(lane < kRedoRows && unit + lane < T && out[(unit + lane) * S] == kRedo);
+        unit = blockIdx.x;
+        const int64_t mine = unit + lane * (int64_t)gridDim.x;
+        todo = (uint32_t)__ballot(lane < SC && mine < T && out[mine * S] == kRedo);
     }
     for (;;) {  // once, and for REDO once per handed-over step
     int64_t t = unit;
     if (REDO) {
         if (todo == 0) return;  // uniform over the workgroup
-        t = unit + __builtin_ctz(todo);
+        t = unit + __builtin_ctz(todo) * (int64_t)gridDim.x;
         todo &= todo - 1;
     }
     if (t >= T) return;  // uniform over the workgroup
     const int64_t* dt = d + t * (int64_t)S * R;
 
+    if (NARROW && !FULL && WG != 768 && S > 1) {
+        // a stage of 2^32 ns and more is one on every rank as a rule, so the
+        // first rank's durations (of up to 64 stages) tell before the step is
+        // read.  (Not for a single stage, where the select alone is saved and
+        // the latency costs 2-3%.)
+        const u64 d0 = (u64)dt[(int64_t)(lane < S ? lane : S - 1) * R];
+        if (__ballot((d0 >> 32) != 0) != 0) {  // uniform over the workgroup
+            if (tid == 0) out[t * S] = kRedo;
+            return;
+        }
+    }
     // R, but unknown to the compiler to be loop-invariant
     auto opaque_R = [&]() {
         int x = R;
@@ -237,7 +286,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
         while (j + U <= sb) sum_rows(std::integral_constant<int, U>{});
         while (j < sb) sum_rows(std::integral_constant<int, 1>{});
     }
-    if (!NARROW) load_stage(sb);
+    if (AHEAD) load_stage(sb);
     for (int i = tid; i < NH * kLagWords; i += WG) (&hist[0][0])[i] = 0;
     if (tid == 0) {
         list_n = 0;
@@ -259,8 +308,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
             // which the 64-bit tests forced); at 32 values, two at a time
             constexpr int CH = WG == 768 ? NLD / 4 : PREFIX ? (K == 16 ? 2 : NLD / 2) : 2;
             // the stage row through a buffer resource: its base in SGPRs, a
-            // lane's offset in one VGPR (FULL: the same for every load)
-            const auto rs = buffer_rsrc(dt + (int64_t)s * R, (uint32_t)R * 8u);
+            // lane's offset in one VGPR (FULL: the same for every load); of
+            // length 0, so that nothing is read, once the step is handed over
+            const auto rs = buffer_rsrc(dt + (int64_t)s * R, wide_step ? 0u : (uint32_t)R * 8u);
             uint32_t mx = 0, mn = ~0u;
             bool wide = false;  // wave-uniform: some value of the wave left 32 bits
 #pragma unroll
@@ -306,6 +356,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
             lmax = wide ? ~0ull : wmax;
             lmin = (u64)(~nmn);
         } else {
+            if (!AHEAD) load_stage(s);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (ok[k / VEC]) {
@@ -314,7 +365,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
                     lmin = umin64(lmin, P[k]);
                 }
             }
-            if (s + 1 < s1) load_stage(s + 1);
+            if (AHEAD && s + 1 < s1) load_stage(s + 1);
             // block max and min (min as the max of complements)
             lmax = group_max<64>(lmax);
             lmin = ~group_max<64>(~lmin);
@@ -332,12 +383,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
         const u64 F = lane0(group_max<16>(has ? red_max[pb][wl] : 0ull));
         const u64 Pmin = ~lane0(group_max<16>(has ? ~red_min[pb][wl] : 0ull));
         // a value left 32 bits (uniform: every wave read the same
-        // partials); the step runs on, on values that no longer matter, and
-        // is handed over at its end (an exit here costs the narrow lag 22
-        // VGPRs of spills)
+        // partials): no further loads and selects, and the step is handed
+        // over at its end (an exit here costs the narrow lag 22 VGPRs of
+        // spills)
         if (NARROW) wide_step = wide_step || (F >> 32) != 0;
         // rebase: from here on P holds u = P - Pmin (the minimum is 0)
-        const u64 range = F - Pmin;
+        const u64 range = NARROW && wide_step ? 0 : F - Pmin;
         const int Rs = NARROW ? opaque_R() : R;
 #pragma unroll
         for (int k = 0; k < K; ++k) P[k] = !NARROW || real(k, Rs) ? P[k] - (V)Pmin : (V)range;
@@ -531,7 +582,7 @@ template <bool PREFIX, bool REDO>
 __global__ __launch_bounds__(kStreamWG) void k_median_stream(const int64_t* __restrict__ d,
                                                              int64_t T, int R, int S,
                                                              int64_t* __restrict__ out,
-                                                             int64_t* __restrict__ out_inc)
+                                                             int64_t* __restrict__ out_inc, int SC)
 {
     constexpr int NW = kStreamWG / 64;
     __shared__ __attribute__((aligned(16))) uint32_t hist[kSelWords];
@@ -543,10 +594,10 @@ __global__ __launch_bounds__(kStreamWG) void k_median_stream(const int64_t* __re
     const int lane = tid & 63;
     const int wave = tid >> 6;
     // REDO: the steps of this workgroup that the narrow pass handed over
-    const int64_t unit = REDO ? (int64_t)blockIdx.x * kRedoRows : blockIdx.x;
-    uint32_t todo = REDO ? (uint32_t)__ballot(lane < kRedoRows && unit + lane < T && out[(unit + lane) * S] == kRedo) : 1u;
+    const int64_t unit = blockIdx.x, mine = unit + lane * (int64_t)gridDim.x;
+    uint32_t todo = REDO ? (uint32_t)__ballot(lane < SC && mine < T && out[mine * S] == kRedo) : 1u;
     for (; todo != 0; todo &= todo - 1) {
-    const int64_t t = unit + __builtin_ctz(todo);
+    const int64_t t = unit + __builtin_ctz(todo) * (int64_t)gridDim.x;
     if (t >= T) return;
     const int64_t* dt = d + t * (int64_t)S * R;
     for (int i = tid; i < kSelWords; i += kStreamWG) hist[i] = 0;
@@ -756,6 +807,7 @@ static int launch_lag(const int64_t* d, int64_t T, int R, int S, int64_t* out, i
                       sf_stream_t stream)
 {
     const int64_t waves = T * (R <= 1024 ? 1 : R >= 16384 ? 16 : (R + 1023) / 1024);
+    const int stages = S;
     int64_t units = 1;
     int SC = S;
     if (PREFIX) {
@@ -774,8 +826,11 @@ static int launch_lag(const int64_t* d, int64_t T, int R, int S, int64_t* out, i
     const LagVariant v = vec2 ? pick_lag<PREFIX, 2>(T, R, split) : pick_lag<PREFIX, 1>(T, R, split);
     void* args[] = {(void*)&d, (void*)&T, (void*)&R, (void*)&S, (void*)&out, (void*)&out_inc, (void*)&SC};
     int rc = launch(v.fn, dim3((unsigned)(T * units)), dim3(v.WG), args, 0, stream);
-    if (rc == SF_OK && v.redo)
-        rc = launch(v.redo, dim3((unsigned)((T + kRedoRows - 1) / kRedoRows)), dim3(v.redo_WG), args, 0, stream);
+    if (rc == SF_OK && v.redo) {
+        const RedoGrid g = redo_grid(T, v.redo_WG / 64, R > 16384, S == 1 ? stages : 1);
+        SC = g.rows;
+        rc = launch(v.redo, dim3((unsigned)g.blocks), dim3(v.redo_WG), args, 0, stream);
+    }
     return rc;
 }
 

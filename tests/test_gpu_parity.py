@@ -996,6 +996,54 @@ def test_narrow_pass_hand_over(sf, R):
     assert_spread_equal(sf, wide, 2)
 
 
+# (R, S, T) whose lag is not split by stages, so that it takes the 32-bit pass
+# and its hand-over: odd and even partly filled tiles, full ones, both shapes
+# past 16384 ranks; the last ones with more steps than workgroups hand over
+LAG_HAND_OVER = [(4099, 2, 430), (4100, 2, 430), (8191, 2, 270), (8192, 3, 270), (8193, 2, 240), (16383, 2, 135),
+                 (16384, 3, 135), (16387, 3, 5), (16388, 2, 300), (32768, 2, 3), (4097, 1, 2070), (4098, 1, 4150),
+                 (16385, 1, 2060)]
+
+
+@pytest.mark.parametrize("R,S,T", LAG_HAND_OVER)
+def test_lag_hand_over(sf, R, S, T):
+    """The lag's hand-over where its steps are not split: single marked steps
+    (a duration of 2^32 or more at the first rank, which tells before the step
+    is read, or at another), prefixes that carry past 2^32 one stage after the
+    other, a stretch of marked steps, every third one, the largest values that
+    are not handed over; then every step marked."""
+    rng = np.random.Generator(np.random.PCG64(R * 3 + S))
+    d = rng.integers(0, 10**7, size=(T, S, R), dtype=np.int64)
+    d[1, S - 1, R // 3] = (1 << 32) + 5
+    if T > 4:
+        d[2, 0, 0] = 1 << 40
+        d[3, :, R - 1] = 3 * 10**9                       # carries at the second stage
+        d[4, 0, R - 2] = (1 << 32) - 1
+    if T > 40:
+        d[10:30, S // 2] = 6 * 10**9 + rng.integers(0, 6 * 10**8, size=(20, R))
+        d[40:T - 5:3, 0, 1:] += 1 << 33
+    print("case R=%d S=%d T=%d mixed" % (R, S, T), flush=True)
+    assert_lag_equal(sf, d)
+    d[:, S - 1] += 1 << 33
+    print("case R=%d S=%d T=%d all handed over" % (R, S, T), flush=True)
+    assert_lag_equal(sf, d)
+
+
+@pytest.mark.parametrize("R,S,T", [(513, 6, 800), (513, 8, 1300), (514, 1, 4200), (1023, 7, 1250), (1025, 6, 700),
+                                   (2047, 5, 2100), (4097, 6, 360), (16385, 2, 1100)])
+def test_spread_hand_over(sf, R, S, T):
+    """The raw spread's hand-over with more marked rows or steps than it has
+    workgroups: one long stage in every step, then rows marked at random."""
+    rng = np.random.Generator(np.random.PCG64(R * 5 + S))
+    d = rng.integers(0, 10**7, size=(T, S, R), dtype=np.int64)
+    d[:, S // 2] += 5 * 10**9
+    print("case R=%d S=%d T=%d one stage" % (R, S, T), flush=True)
+    assert_spread_equal(sf, d, 100)
+    d[:, S // 2] -= 5 * 10**9
+    t, s = np.nonzero(rng.random((T, S)) < 0.3)
+    d[t, s, rng.integers(0, R, size=len(t))] = (1 << 32) + t
+    print("case R=%d S=%d T=%d random rows" % (R, S, T), flush=True)
+    assert_spread_equal(sf, d, 100)
+
 
 @pytest.mark.parametrize("R", [16385, 16386, 20000, 32767, 32768, 40000, 65536])
 def test_lag_spread_past_16384_ranks(sf, R):

@@ -1,0 +1,54 @@
+"""The library's dispatch on the host: which kernels a call launches, and how
+many workgroups (no GPU; see launches.py)."""
+import re
+
+import pytest
+
+from launches import build_recorder, launches
+from test_gpu_parity import LAG_HAND_OVER
+
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return build_recorder(tmp_path_factory.mktemp("recorder"))
+
+
+def template_args(name):
+    return [a.strip() for a in re.search(r"<(.*)>", name).group(1).split(",")]
+
+
+def is_narrow(name):
+    return name.startswith("k_median_spread") and template_args(name)[7] == "true"
+
+
+def test_lag_hand_over_shapes_take_the_narrow_pass(recorder):
+    """The shapes of the GPU test of the lag's hand-over are handed over: the
+    32-bit pass first, then the 64-bit kernel."""
+    cases = [("sf_frontier_lag", R, S, T, 1) for R, S, T in LAG_HAND_OVER]
+    for c, ls in zip(cases, launches(recorder, cases)):
+        assert len(ls) == 2 and is_narrow(ls[0].name), (c, ls)
+
+
+@pytest.mark.parametrize("call", ["sf_frontier_lag", "sf_rank_spread"])
+def test_hand_over_is_as_wide_as_the_chip(recorder, call):
+    """With every step handed over, its workgroups are through in little more
+    than the rounds that a workgroup per step would take, and there are few
+    enough of them where nothing is handed over."""
+    cases = [(call, R, S, T, 100) for R in (513, 1023, 1024, 3000, 4097, 8192, 12289, 16384, 24576, 32767)
+             for S in (1, 6, 8, 12) for T in (1, 64, 256, 300, 500, 512, 1000, 2000, 4000, 10000, 50000)]
+    seen = 0
+    for c, ls in zip(cases, launches(recorder, cases)):
+        if not is_narrow(ls[0].name):
+            continue
+        seen += 1
+        steps, redo = ls[0].grid, ls[1]
+        waves = 32 if redo.name.startswith("k_median_stream") else 16  # resident per CU
+        at_once = CUS * waves * 64 // redo.block
+        rows = -(-steps // redo.grid)
+        assert rows <= 8
+        depth = rows if redo.grid <= at_once else steps / at_once + rows - 1
+        assert depth <= 1.25 * -(-steps // at_once) + 2, (c, ls)
+        assert redo.grid <= max(4096, steps // 4), (c, ls)
+    assert seen > 50
