@@ -306,7 +306,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
             // (with the select's tests in 32 bits this fits the 64-VGPR
             // budget; measured at 16384 ranks 3% faster than two at a time,
             // which the 64-bit tests forced); at 32 values, two at a time
-            constexpr int CH = WG == 768 ? NLD / 4 : PREFIX ? (K == 16 ? 2 : NLD / 2) : 2;
+            constexpr int CH = WG == 768 ? (PREFIX ? NLD / 2 : NLD / 4) : PREFIX ? (K == 16 ? 2 : NLD / 2) : 2;
             // the stage row through a buffer resource: its base in SGPRs, a
             // lane's offset in one VGPR (FULL: the same for every load); of
             // length 0, so that nothing is read, once the step is handed over

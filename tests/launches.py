@@ -10,6 +10,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(os.path.dirname(HERE), "paper_2606_06751_amd", "libstagefrontier.so")
 
+LLVM = "/opt/rocm/llvm/bin/"
 Launch = collections.namedtuple("Launch", "name grid block lds")
 
 
@@ -48,3 +49,27 @@ def launches(recorder, cases, lib=LIB):
     for c, (rc, _) in zip(cases, res):
         assert rc == 0, (c, rc)
     return [[Launch(short[n], g, b, l) for n, g, b, l in ls] for _, ls in res]
+
+
+def spilled_vgprs(folder, lib=LIB):
+    """Spilled vector registers of every kernel in the built library, from the
+    metadata of its code objects."""
+    data = open(lib, "rb").read()
+    out, at = {}, data.find(b"\x7fELF", 4)
+    while at >= 0:
+        if int.from_bytes(data[at + 18:at + 20], "little") == 224:  # an AMDGPU code object
+            end = data.find(b"\x7fELF", at + 4)
+            path = os.path.join(str(folder), "object.elf")
+            with open(path, "wb") as fh:
+                fh.write(data[at:end if end > 0 else len(data)])
+            notes = subprocess.run([LLVM + "llvm-readelf", "--notes", path], capture_output=True, text=True).stdout
+            name = None
+            for line in notes.split("\n"):
+                key, _, value = line.strip().lstrip("- ").partition(":")
+                if key == ".name" and value.strip().startswith("_Z"):
+                    name = value.strip()
+                elif key == ".vgpr_spill_count" and name:
+                    out[name] = int(value)
+        at = data.find(b"\x7fELF", at + 4)
+    plain = subprocess.run(["c++filt"] + list(out), capture_output=True, text=True, check=True).stdout.split("\n")
+    return {d.replace("void ", "").replace("sfk::", "").split("(")[0]: n for d, n in zip(plain, out.values())}

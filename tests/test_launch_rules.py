@@ -4,7 +4,7 @@ import re
 
 import pytest
 
-from launches import build_recorder, launches
+from launches import build_recorder, launches, spilled_vgprs
 from test_gpu_parity import LAG_HAND_OVER
 
 CUS = 256
@@ -17,6 +17,15 @@ def recorder(tmp_path_factory):
 
 def template_args(name):
     return [a.strip() for a in re.search(r"<(.*)>", name).group(1).split(",")]
+
+
+@pytest.fixture(scope="module")
+def spills(tmp_path_factory):
+    return spilled_vgprs(tmp_path_factory.mktemp("objects"))
+
+
+def kernels(recorder, call, R, S, T, window=1):
+    return [ls.name for ls in launches(recorder, [(call, R, S, T, window)])[0]]
 
 
 def is_narrow(name):
@@ -52,3 +61,14 @@ def test_hand_over_is_as_wide_as_the_chip(recorder, call):
         assert depth <= 1.25 * -(-steps // at_once) + 2, (c, ls)
         assert redo.grid <= max(4096, steps // 4), (c, ls)
     assert seen > 50
+
+
+def test_hand_over_kernels_spill_nothing(spills):
+    redo = {k: n for k, n in spills.items() if k.startswith("k_median_spread") and template_args(k)[8] == "true"}
+    assert len(redo) >= 14 and not any(redo.values()), redo
+
+def test_twelve_wave_lag_keeps_its_registers(spills):
+    """More than 16384 ranks, 80 VGPRs: two loads of a stage at once (four
+    spilled 20 to 24)."""
+    twelve = {k: n for k, n in spills.items() if k.startswith("k_median_spread") and template_args(k)[3] == "768"}
+    assert len(twelve) == 4 and max(twelve.values()) <= 10, twelve
