@@ -53,7 +53,7 @@ namespace sfk {
 //      data contract into *status; GTAB: partial maxima in the out_increment
 //      rows instead of LDS (any S; G <= 64); D: stage rows in flight.
 template <int VEC, int K, int G, int WG, bool CHECK, bool GTAB, int D>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(K == 16 && G == 32 ? 4 : 1))) void k_frontier(const int64_t* __restrict__ d, int64_t T,
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(K == 16 && G == 32 && !CHECK ? 4 : 1))) void k_frontier(const int64_t* __restrict__ d, int64_t T,
                                                  int R, int S, int64_t* __restrict__ inc,
                                                  int32_t* __restrict__ lead,
                                                  uint32_t* __restrict__ status)

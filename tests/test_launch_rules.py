@@ -72,3 +72,7 @@ def test_twelve_wave_lag_keeps_its_registers(spills):
     spilled 20 to 24)."""
     twelve = {k: n for k, n in spills.items() if k.startswith("k_median_spread") and template_args(k)[3] == "768"}
     assert len(twelve) == 4 and max(twelve.values()) <= 10, twelve
+
+def test_checked_frontier_spills_nothing(spills):
+    checked = {k: n for k, n in spills.items() if k.startswith("k_frontier<") and template_args(k)[4] == "true"}
+    assert len(checked) >= 20 and not any(checked.values()), checked
