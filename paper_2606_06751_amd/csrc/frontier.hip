@@ -241,8 +241,12 @@ FrontierVariant variant(int per_cu)
 // TB/s, 2049: 2.6 -> 7.0, 1030: 5.0 -> 5.8); near the full tile the wide ones
 // stay ahead once the rows of all steps reach 32 MB (R = 1024: 7.07 against
 // 6.80 TB/s; below, at 16 MB, 6.2 against 6.3, at 4 MB 3.0 against 4.8).
+// Shapes with several rows in flight (D > 1) want stages to keep them there:
+// from 1025 to 1792 ranks eight (1500 x 3000 steps, 4 stages 26 : 33 us, 6 36 :
+// 41, 8 47 : 46), from 4097 to 5120 four (5120 x 3000, 2 stages 54 : 63, 6 129 :
+// 124).
 template <bool CHECK>
-FrontierVariant pick_frontier(int R, int64_t row_bytes)
+FrontierVariant pick_frontier(int R, int S, int64_t row_bytes)
 {
     const bool many = row_bytes >= 32 << 20;
     if (R == 1) return variant<CHECK, 2, 4, 64, false, 1, 1>(0);
@@ -254,10 +258,10 @@ FrontierVariant pick_frontier(int R, int64_t row_bytes)
     if (R <= 256) return variant<CHECK, 16, 32, 256>(4);
     if (R <= 512) return variant<CHECK, 4, 256, 256>(0);
     if (R <= 1024) return R > 896 && many ? variant<CHECK, 32, 64, 256>(6) : variant<CHECK, 4, 256, 256>(0);
-    if (R <= 1792) return variant<CHECK, 4, 512, 512, false, 4>(0);
+    if (R <= 1792 && S >= 8) return variant<CHECK, 4, 512, 512, false, 4>(0);
     if (R <= 2048) return variant<CHECK, 8, 512, 512>(0);
     if (R <= 4096) return R > 3840 && many ? variant<CHECK, 32, 256, 256>(0) : variant<CHECK, 8, 512, 512>(0);
-    if (R <= 5120) return variant<CHECK, 8, 1024, 1024, false, 2>(0);
+    if (R <= 5120 && S >= 4) return variant<CHECK, 8, 1024, 1024, false, 2>(0);
     return variant<CHECK, 32, 64, 64>(3);
 }
 
@@ -285,10 +289,13 @@ FrontierVariant pick_frontier_deep(int R)
 // chip idles (16384 ranks x 12 stages: 64 steps 87 -> 31 us, 256 steps 99 ->
 // 63, 512 steps 115 -> 119).  Up to 4096 ranks the rows in flight are worth
 // their registers while the stage rows of all steps are within 4 MB and there
-// are more stages than rows in flight (130 x 100 stages: 1024 steps 66 -> 28
-// us, 4096 steps 88 -> 80; 40 x 8: 3.6 -> 4.0); from 513 ranks twice as many
-// stages (1024 x 8: 4.3 against 5.1); at 129 to 256 ranks they also win at
-// few stages up to 2 MB (250 x 8: 256 steps 5.7 -> 4.7 us, 4096 steps 11.5 ->
+// are enough stages to keep them in flight (130 x 100 stages: 1024 steps 66 ->
+// 28 us, 4096 steps 88 -> 80); at few ranks that takes more of them, since a
+// wave holds several steps' rows without it (2 ranks x 100000 steps: 9 stages
+// 8.4 -> 11.5 us, 24 26.5 -> 28.3, 48 71.7 -> 58.8; 8 x 8192: 16 4.6 -> 5.1, 24
+// 8.6 -> 7.1; 16 x 2048: 12 3.8 -> 4.3, 24 6.4 -> 6.0; 33 x 8192: 9 6.9 -> 7.8, 16
+// 11.2 -> 10.1; 1024 x 8: 4.3 against 5.1); at 129 to 256 ranks they also win
+// at few stages up to 2 MB (250 x 8: 256 steps 5.7 -> 4.7 us, 4096 steps 11.5 ->
 // 14.5).
 static bool deep_steps(int64_t T, int R, int S)
 {
@@ -296,7 +303,8 @@ static bool deep_steps(int64_t T, int R, int S)
     if (R == 1) return false;
     if (R > 4096) return T < 400;
     if (R > 128 && R <= 256 && row <= 2 << 20) return true;
-    return S > (R > 512 ? 16 : 8) && row <= 4 << 20;
+    const int few = R <= 8 ? 24 : R <= 16 ? 16 : R <= 32 ? 8 : R <= 64 ? 12 : R <= 128 ? 9 : R <= 256 ? 8 : R <= 512 ? 12 : 16;
+    return S > few && row <= 4 << 20;
 }
 
 // Stage counts whose LDS table would exceed what a workgroup may hold: the
@@ -343,7 +351,7 @@ static int frontier_launch(const int64_t* durations, int64_t T, int32_t R, int32
     const FrontierVariant v =
         gtab   ? (status ? pick_frontier_gtab<true>(R) : pick_frontier_gtab<false>(R))
         : deep ? (status ? pick_frontier_deep<true>(R) : pick_frontier_deep<false>(R))
-               : (status ? pick_frontier<true>(R, row) : pick_frontier<false>(R, row));
+               : (status ? pick_frontier<true>(R, S, row) : pick_frontier<false>(R, S, row));
     const int spw = v.WG / v.G;
     const int sub = v.G < 64 ? v.G : 64;
     const int64_t blocks = (T + spw - 1) / spw;

@@ -301,6 +301,14 @@ def test_frontier_shape_rules(sf, R, S, T):
     assert int(status) == 0
 
 
+@pytest.mark.parametrize("R,S,T", [
+    (2, 24, 70), (2, 25, 70), (7, 25, 9), (9, 16, 40), (16, 17, 40), (33, 12, 9), (34, 13, 9), (100, 9, 50), (101, 10, 50),
+    (400, 12, 20), (401, 13, 20), (1500, 7, 5), (1501, 8, 5), (4098, 3, 402), (5119, 4, 401)])
+def test_frontier_shape_ends(sf, R, S, T):
+    """Both sides of the stage counts from which rows are kept in flight."""
+    test_frontier_shape_rules(sf, R, S, T)
+
+
 def test_frontier_chunks_compose(sf):
     """Step-axis chunks written into one output equal a single call."""
     T, S, R = 101, 12, 640

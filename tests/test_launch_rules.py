@@ -76,3 +76,12 @@ def test_twelve_wave_lag_keeps_its_registers(spills):
 def test_checked_frontier_spills_nothing(spills):
     checked = {k: n for k, n in spills.items() if k.startswith("k_frontier<") and template_args(k)[4] == "true"}
     assert len(checked) >= 20 and not any(checked.values()), checked
+
+@pytest.mark.parametrize("R,S,T,rows", [
+    (2, 9, 100000, 1), (2, 48, 100000, 8), (8, 16, 8192, 1), (8, 25, 8192, 8), (16, 12, 2048, 1), (16, 17, 2048, 8),
+    (32, 9, 2048, 8), (33, 9, 8192, 1), (64, 13, 2048, 8), (100, 9, 2048, 1), (128, 12, 2048, 8), (200, 9, 2000, 8),
+    (512, 12, 64, 1), (512, 13, 64, 8), (1500, 4, 3000, 1), (1500, 8, 3000, 4), (5120, 2, 3000, 1), (5120, 4, 3000, 2)])
+def test_frontier_rows_in_flight(recorder, R, S, T, rows):
+    """Rows kept in flight take as many stages as pay for them."""
+    (name,) = kernels(recorder, "sf_frontier", R, S, T)
+    assert template_args(name)[6] == str(rows), name
