@@ -349,15 +349,22 @@ size_t ev_lds_need(const EvidenceVariant& v, int R, int S, bool gtab)
 }
 
 // Few steps (measured on MI355X): a wave or more per step and four rows in
-// flight, where the shapes below leave the chip idle, up to 1 MB (256 ranks: 2
-// MB) of stage rows over all steps (1023 x 8 x 128 26 -> 12 us, 130 x 60 x 128
-// 120 -> 41; at 8 MB 27 -> 36); past 8192 ranks all 1024 lanes.  From 1025 to
-// 8192 ranks the reductions of so many waves cost more than they hide.
-static bool ev_deep(int64_t T, int R)
+// flight, where the shapes below leave the chip idle (1023 ranks x 8 x 128 26 ->
+// 12 us, 130 x 60 x 128 120 -> 41).  Up to 1 MB of stage rows over all steps (at 8
+// MB 27 -> 36); at 129 to 256 ranks, where the shapes below take two tiles, up
+// to 1536 steps (200 x 12 x 1200 26 -> 22, 129 x 6 x 2000 14.3 -> 15.6); up to 128
+// ranks, one wave per step, up to 1024 steps (100 x 12: 600 steps 13.8 -> 10.8,
+// 1200 14.7 -> 16.1).  Past 8192 ranks all 1024 lanes, one workgroup per CU, up
+// to 256 steps (16384 x 8: 150 steps 46 -> 40, 300 74 -> 86) and where the last
+// tile is half full at least (24576 x 8 x 50 66 -> 74, 32768 88 -> 81).  From 1025
+// to 8192 ranks the reductions of so many waves cost more than they hide.
+static bool ev_deep(int64_t T, int R, int S)
 {
-    const int64_t row = T * R * 8;
-    if (R > 8192) return T < 400;
-    return R > 64 && R <= 1024 && row <= (R <= 256 ? 2 << 20 : 1 << 20);
+    if (R > 8192) return T <= 256 && (R - 1) % 16384 >= 8192;
+    if (R <= 64 || R > 1024) return false;
+    if (R <= 128) return T <= 1024 && S >= 4;
+    if (R <= 256) return T <= 1536;
+    return T * R * 8 <= 1 << 20 && (R > 512 || S >= 4);
 }
 
 template <int V>
@@ -376,24 +383,24 @@ EvidenceVariant pick_evidence_deep(int R)
 // 16 ranks each, since a reduction costs as much as 8 to 10 slots (1500 x 10
 // x 8192: 356 -> 164 us, 671 x 8 x 8192 85 -> 63, 1024 x 12 x 8192 149 -> 128,
 // 6001 x 10 x 1024 133 -> 84; 250 ranks on 32 lanes level, 256 110 against
-// 115; 8192 ranks at 16 each, 32 MB of rows and more, 126 against 130).  A
+// 115, 240 x 12 x 16000 72 against 67; 8192 ranks at 16 each, 32 MB of rows and more, 126 against 130).  A
 // shape whose LDS would exceed 64 KB at this S falls back to two 64-lane slots per step
 // (80 * S bytes, at most 40 KB).
 template <int V>
 EvidenceVariant pick_evidence(int64_t T, int R, int S)
 {
-    if (ev_deep(T, R)) {
+    if (ev_deep(T, R, S)) {
         const EvidenceVariant v = pick_evidence_deep<V>(R);
         if (ev_lds_need(v, R, S, false) <= kLdsMaxPerWg) return v;
     }
     EvidenceVariant v;
     if (R == 1) v = ev_variant<1, 2, 4, 64>(0);
-    else if (R <= 8) v = ev_variant<V, 2, 4, 64, false, 4>(0);
-    else if (R <= 16) v = ev_variant<V, 2, 8, 64, false, 4>(0);
+    else if (R <= 8) v = S < 8 ? ev_variant<V, 2, 4, 64>(0) : ev_variant<V, 2, 4, 64, false, 4>(0);
+    else if (R <= 16) v = S < 8 ? ev_variant<V, 2, 8, 64>(0) : ev_variant<V, 2, 8, 64, false, 4>(0);
     else if (R <= 32) v = ev_variant<V, 4, 8, 64>(0);
     else if (R <= 64) v = ev_variant<V, 4, 16, 64>(0);
     else if (R <= 128) v = ev_variant<V, 8, 16, 256>(8);
-    else if (R <= 240) v = ev_variant<V, 8, 32, 64>(0);
+    else if (R <= 240 && (R <= 144 || T * R * 8 < 24 << 20)) v = ev_variant<V, 8, 32, 64>(0);
     else if (R <= 256) v = ev_variant<V, 8, 16, 256>(8);
     else if (R <= 384) v = ev_variant<V, 12, 32, 64>(0);
     else if (R <= 512) v = ev_variant<V, 16, 32, 64>(0);

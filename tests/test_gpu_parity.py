@@ -179,6 +179,14 @@ def test_evidence_shape_rules(sf, R, S, T):
 
 
 @pytest.mark.parametrize("R,S,T", [
+    (3, 5, 40), (7, 1, 9), (8, 7, 300), (9, 3, 50), (15, 6, 33), (16, 7, 20), (145, 2, 22000), (239, 1, 13300), (127, 4, 1025),
+    (128, 4, 1024), (200, 3, 1536), (201, 3, 1537), (8193, 2, 256), (8193, 1, 257), (16385, 2, 3), (24577, 1, 2)])
+def test_evidence_shape_ends(sf, R, S, T):
+    """Both sides of where the shapes for few steps and few ranks end."""
+    test_evidence_shape_rules(sf, R, S, T)
+
+
+@pytest.mark.parametrize("R,S,T", [
     (1, 5, 3), (2, 9, 5), (3, 40, 3), (127, 30, 9), (256, 17, 40), (257, 25, 1100), (511, 9, 4), (513, 40, 3),
     (1023, 9, 5), (1025, 5, 6), (2047, 7, 3), (3001, 6, 700), (4095, 12, 2), (4097, 8, 3), (4098, 3, 430),
     (8191, 5, 3), (8193, 4, 130), (16383, 4, 3), (16385, 3, 3), (16387, 2, 258), (24575, 2, 3), (24577, 3, 2),
