@@ -669,9 +669,12 @@ __global__ __launch_bounds__(kSwWG) void k_window_switches(
 }
 
 // Segmented sums over windows of the columns of a [T][C] int64 array and, where
-// given, of a [T] array y: one workgroup per (window, column), y the last;
-// grid-stride.  Bound by the launch: both arrays in one (two launches took
-// 9.2 us of a gain call, one 4.7).
+// given, of a [T] array y: one workgroup per (window, column), those of y
+// last; grid-stride.  Bound by the launch: both arrays in one (two launches
+// took 9.2 us of a gain call, one 4.7); U loads in flight per thread: a gain
+// call of 2 stages x 200000 steps, windows of 20000, takes 46 us with one, 33
+// with four; of 6 x 100000, windows of one step, 461 and 493.
+template <int U>
 __global__ __launch_bounds__(kSumWG) void k_window_sum(const int64_t* __restrict__ x, int64_t T,
                                                        int C, int64_t window, int64_t W,
                                                        int64_t* __restrict__ out,
@@ -680,16 +683,16 @@ __global__ __launch_bounds__(kSumWG) void k_window_sum(const int64_t* __restrict
 {
     __shared__ int64_t part[kSumWG / 64];
     const int tid = threadIdx.x;
-    const int64_t cols = (int64_t)C + (y ? 1 : 0);
-    for (int64_t id = blockIdx.x; id < W * cols; id += gridDim.x) {
-        const int64_t w = id / cols;
-        const int64_t c = id - w * cols;
+    const int64_t nx = W * C, total = nx + (y ? W : 0);
+    for (int64_t id = blockIdx.x; id < total; id += gridDim.x) {
+        const bool of_x = id < nx;
+        const int64_t w = of_x ? id / C : id - nx;
+        const int64_t* col = of_x ? x + (id - w * C) : y;
+        const int64_t stride = of_x ? C : 1;
         const int64_t t0 = w * window;
         const int64_t t1 = min(t0 + window, T);
-        const int64_t* col = c < C ? x + c : y;
-        const int64_t stride = c < C ? C : 1;
         int64_t sum = 0;
-#pragma unroll 4
+#pragma unroll U
         for (int64_t t = t0 + tid; t < t1; t += kSumWG) sum += col[t * stride];
         sum = wave_sum64(sum);
         if ((tid & 63) == 0) part[tid >> 6] = sum;
@@ -697,7 +700,7 @@ __global__ __launch_bounds__(kSumWG) void k_window_sum(const int64_t* __restrict
         if (tid == 0) {
             int64_t acc = 0;
             for (int i = 0; i < kSumWG / 64; ++i) acc += part[i];
-            *(c < C ? out + w * C + c : out_y + w) = acc;
+            *(of_x ? out + id : out_y + w) = acc;
         }
         __syncthreads();
     }
@@ -709,8 +712,10 @@ int launch_window_sum(const int64_t* x, int64_t T, int C, int64_t window, int64_
     const int64_t items = W * ((int64_t)C + (y ? 1 : 0));
     void* args[] = {(void*)&x, (void*)&T,   (void*)&C, (void*)&window,
                     (void*)&W, (void*)&out, (void*)&y, (void*)&out_y};
-    return launch(reinterpret_cast<const void*>(&k_window_sum),
-                  dim3((unsigned)(items < 1048576 ? items : 1048576)), dim3(kSumWG), args, 0, stream);
+    const void* fn = window > 2 * kSumWG ? reinterpret_cast<const void*>(&k_window_sum<4>)
+                                         : reinterpret_cast<const void*>(&k_window_sum<1>);
+    return launch(fn, dim3((unsigned)(items < 1048576 ? items : 1048576)), dim3(kSumWG), args, 0,
+                  stream);
 }
 
 }  // namespace sfk

@@ -1470,3 +1470,16 @@ def test_median_tile_edges(sf, window):
             d[:, 0, 4] = rng.integers(0, 1 << 47, size=T)              # wide
         print("case window=%d T=%d S=%d R=%d" % (window, T, S, R), flush=True)
         assert_median_equal(sf, d, window)
+
+
+@pytest.mark.parametrize("window", [1, 3, 512, 513, 1025, 3000])
+def test_window_sums_of_gain_and_spread(sf, window):
+    """The window sums of a [T][S] array and a [T] one, on both sides of the
+    window from which several steps are loaded at once."""
+    rng = np.random.Generator(np.random.PCG64(window))
+    T, S, R = 2601, 3, 5
+    d = rng.integers(0, 10**6, size=(T, S, R), dtype=np.int64)
+    bt = rng.integers(0, 10**6, size=(-(-T // window), S, R), dtype=np.int64)
+    print("case window=%d" % window, flush=True)
+    assert_gain_equal(sf, d, bt, window)
+    assert_spread_equal(sf, d, window)

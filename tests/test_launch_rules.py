@@ -96,3 +96,7 @@ def test_evidence_shapes(recorder, R, S, T, shape):
     be the faster ones."""
     (name,) = kernels(recorder, "sf_frontier_evidence", R, S, T)
     assert ", ".join(template_args(name)[1:]) == shape, name
+
+def test_window_sum_of_short_windows_is_not_unrolled(recorder):
+    assert kernels(recorder, "sf_rank_spread", 16, 6, 100000, 1)[-1] == "k_window_sum<1>"
+    assert kernels(recorder, "sf_rank_spread", 16, 2, 200000, 20000)[-1] == "k_window_sum<4>"
