@@ -169,18 +169,26 @@ __global__ __launch_bounds__(kTopWG) void k_window_top2(const int64_t* __restric
 // 2500: 15.4 -> 9.6 / 20.9 -> 9.8.  It takes windows whose table fits the LDS
 // of a CU and whose rows one workgroup reads in about the time of the other
 // kernels (a single window of 4000 x 12: 12.5 against 12.7 us), more of them
-// where several windows run at once.
+// where several windows run at once.  For the counts, whose other kernels read
+// a window's stages with a workgroup each, that depends on the stages (64
+// ranks, one window, in us, here and there: 250 x 68 7.6 : 7.6, with windows of
+// 250 x 260 four 17.8 : 9.6, sixteen 18.2 : 21.2), and on the ranks, since one
+// wave looks through the row of a chosen stage (one stage of 4096 ranks 8.0 :
+// 7.4, 8192 11.7 : 8.5, 16384 19.5 : 11.1; six of 6000 11.8 : 9.7).
 constexpr int kWholeWG = 1024;
 constexpr size_t kWholeLds = 144 * 1024;
-constexpr int64_t kWholeEntries = 32768;  // steps x stages of one window; twice that from four windows up
+constexpr int64_t kWholeEntries = 32768;  // steps x stages of one window; twice that with several windows
 
 static size_t whole_lds(int R, int S, size_t entry) { return (size_t)S * 8 + (size_t)S * R * entry; }
-static bool whole_fits(int64_t T, int R, int S, int64_t window, size_t entry)
+static bool whole_fits(int64_t T, int R, int S, int64_t window, bool weighted)
 {
     const int64_t n = window < T ? window : T;
-    const int64_t most = T / n >= 4 ? 2 * kWholeEntries : kWholeEntries;
-    return S <= kWholeWG && n <= most / S && (int64_t)S * R <= (int64_t)kWholeLds &&
-           whole_lds(R, S, entry) <= kWholeLds;
+    const int64_t W = T / n;
+    if (S > kWholeWG || (int64_t)S * R > (int64_t)kWholeLds || whole_lds(R, S, weighted ? 8 : 4) > kWholeLds) return false;
+    if (weighted) return R <= 12288 && n <= (W >= 4 ? 2 : 1) * kWholeEntries / S;
+    if (R > 6144 || (R > 4096 && S * R > 12288)) return false;
+    if (W >= 16) return n <= 2 * kWholeEntries / S;
+    return n <= kWholeEntries / S && n * (S - 4) <= (W >= 4 && S * R <= 8192 ? 16384 : 12288);
 }
 
 template <bool WEIGHTED>
@@ -748,7 +756,7 @@ SF_API int sf_window_summary(const int64_t* increment, const int32_t* leader, in
         for (int b = (a < 2 ? 2 : a + 1); b < 5; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
 
-    if (whole_fits(T, R, S, window, 4))
+    if (whole_fits(T, R, S, window, false))
         return launch_whole<false>(increment, leader, T, R, S, window, W, out_stage_exposed, out_lead_counts,
                                    nullptr, out_top2, stream);
     const int nchunk = (R + kHistChunk - 1) / kHistChunk;
@@ -789,7 +797,7 @@ SF_API int sf_window_lead_exposed(const int64_t* increment, const int32_t* leade
         for (int b = (a < 2 ? 2 : a + 1); b < 4; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
 
-    if (whole_fits(T, R, S, window, 8))
+    if (whole_fits(T, R, S, window, true))
         return launch_whole<true>(increment, leader, T, R, S, window, W, nullptr, nullptr, out_lead_exposed,
                                   out_top2, stream);
     const int nchunk = (R + kLeadChunk - 1) / kLeadChunk;

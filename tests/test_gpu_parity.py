@@ -480,6 +480,15 @@ def test_window_whole_edges(sf, R, S, T, window):
         np.testing.assert_array_equal(g.cpu().numpy(), o)
 
 
+@pytest.mark.parametrize("R,S,T,window", [
+    (4097, 2, 40, 9), (4097, 3, 40, 9), (6144, 2, 30, 9), (6145, 1, 30, 9), (12288, 1, 20, 9), (12289, 1, 20, 9),
+    (20, 68, 2400, 200), (20, 68, 800, 200), (200, 68, 800, 200), (3, 260, 1000, 250), (3, 260, 4250, 250)])
+def test_window_whole_ends(sf, R, S, T, window):
+    """Both sides of the rank and stage counts up to which a workgroup takes a
+    whole window."""
+    test_window_whole_edges(sf, R, S, T, window)
+
+
 def test_lead_exposed_ties_signs_and_out_of_range_leaders(sf):
     """Stage-total ties, rank ties on exposed time, zero rows (rank -1),
     negative advances (never a suspect) and leaders outside [0, R)."""

@@ -100,3 +100,14 @@ def test_evidence_shapes(recorder, R, S, T, shape):
 def test_window_sum_of_short_windows_is_not_unrolled(recorder):
     assert kernels(recorder, "sf_rank_spread", 16, 6, 100000, 1)[-1] == "k_window_sum<1>"
     assert kernels(recorder, "sf_rank_spread", 16, 2, 200000, 20000)[-1] == "k_window_sum<4>"
+
+@pytest.mark.parametrize("call,R,S,T,window,whole", [
+    ("sf_window_summary", 4096, 1, 100, 50, True), ("sf_window_summary", 8192, 1, 100, 50, False),
+    ("sf_window_summary", 16384, 1, 55, 55, False), ("sf_window_summary", 6000, 6, 50, 50, False),
+    ("sf_window_summary", 6144, 2, 500, 250, True), ("sf_window_summary", 15, 260, 1000, 250, False),
+    ("sf_window_summary", 15, 260, 4000, 250, True), ("sf_window_summary", 361, 68, 250, 250, False),
+    ("sf_window_summary", 60, 68, 1000, 250, True), ("sf_window_summary", 128, 6, 100000, 1000, True),
+    ("sf_window_lead_exposed", 16384, 1, 100, 50, False), ("sf_window_lead_exposed", 15, 260, 1000, 250, True)])
+def test_whole_windows(recorder, call, R, S, T, window, whole):
+    """One workgroup per window where that is the faster way."""
+    assert kernels(recorder, call, R, S, T, window)[0].startswith("k_window_whole") == whole
