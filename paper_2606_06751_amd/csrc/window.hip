@@ -291,23 +291,31 @@ static int launch_whole(const int64_t* inc, const int32_t* lead, int64_t T, int 
                   dim3(kWholeWG), args, whole_lds(R, S, WEIGHTED ? 8 : 4), stream);
 }
 
-// Fused frontier pass and window summary for the smallest inputs: one
-// workgroup of 1024 threads per window does the whole path of Sec. 3 for the
-// window's steps.  Groups of G lanes own a step (K ranks per lane, one rank
-// tile, the packed keys and DPP maxima of k_frontier), loading a chunk of
-// stage rows at once; the group's last lane writes each boundary's advance and
-// leader as soon as the stage is reduced and adds them into the window's LDS
-// totals and lead counts; then the workgroup writes the counts and picks the
-// top-2.  One launch instead of two, where the workgroup takes the window in
-// one round of 256 steps with every row in flight at once (8 ranks x 6 x 1000,
-// windows of 100: 6.1 against 7.1 us).  A second round or chunk of rows costs
-// a memory latency in series and leaves the other CUs idle: windows of 1000 of
-// the same 17.7 against 8.4 us, 15 ranks 8.0 against 7.1, 256 ranks x 6 x 300
-// 63.8 against 9.0.
-constexpr int kFusedMaxR = 8;
-constexpr int kFusedMaxS = 8;
+// Fused frontier pass and window summary for small inputs: one workgroup of
+// 1024 threads per window does the whole path of Sec. 3 for the window's steps.
+// Groups of G lanes own a step (K ranks per lane, one rank tile, the packed
+// keys and DPP maxima of k_frontier), loading a chunk of stage rows at once;
+// the group's last lane writes each boundary's advance and leader as soon as
+// the stage is reduced and adds them into the window's LDS totals and lead
+// counts; then the workgroup writes the counts and picks the top-2.  One launch
+// instead of two (8 ranks x 6 x 1000, windows of 100: 6.1 against 7.1 us).  It
+// takes windows whose steps x stages are about one round of steps, since
+// further rounds, and chunks of rows, cost a memory latency each in series while
+// the other CUs idle; measured against the two launches, in us: 16 ranks x 6,
+// windows of 50 6.0 : 7.6, of 200 9.5 : 7.2; 32 x 6, of 20 5.8 : 7.2, of 100 9.2 :
+// 7.3; 64 x 4, of 20 6.6 : 7.7, of 50 9.1 : 7.6; 256 x 4, of 10 7.2 : 8.5, of 50
+// 12.5 : 8.9; 8 x 12, of 50 7.4 : 7.6, of 200 9.7 : 8.5.
+constexpr int kFusedMaxR = 256;
+constexpr int kFusedMaxS = 12;
 constexpr int64_t kFusedMaxWindow = 256;
 constexpr int64_t kFusedMaxSamples = 1 << 20;
+
+static bool fused_fits(int64_t T, int R, int S, int64_t window)
+{
+    const int64_t n = window < T ? window : T;
+    if (R > kFusedMaxR || S > kFusedMaxS || n > kFusedMaxWindow || T * S * (int64_t)R > kFusedMaxSamples) return false;
+    return n * S <= (R <= 8 ? 2048 : R <= 16 ? 640 : R <= 32 ? 300 : R <= 64 ? 120 : 80);
+}
 
 constexpr int kFusedWG = 1024;  // threads of the fused kernel: 1024 / G steps per round
 
@@ -340,7 +348,7 @@ __global__ __launch_bounds__(kFusedWG) void k_frontier_summary(
     static_assert(K % VEC == 0 && G <= 32, "one DPP group per step");
     constexpr int SPW = kFusedWG / G;  // steps per round
     constexpr int NLD = K / VEC;
-    constexpr int CH = 16 / K;  // stage rows loaded at once
+    constexpr int CH = K >= 8 ? 1 : 16 / K;  // stage rows loaded at once (up to 16 values per lane)
     __shared__ u64 ex_sh[kFusedMaxS];
     __shared__ int32_t cnt_sh[kFusedMaxS * kFusedMaxR];
     const int tid = threadIdx.x;
@@ -431,8 +439,8 @@ __global__ __launch_bounds__(kFusedWG) void k_frontier_summary(
             // wave 0 alone picks the top-2 with DPP wave maxima (no block
             // barriers): the stage of the largest total (a second max takes
             // the lowest stage among the lanes holding it, one stage per
-            // lane), then its most frequent leader (the lowest rank on equal
-            // counts)
+            // lane), then its most frequent leader (up to four ranks per lane,
+            // the lowest rank on equal counts)
             const int lane = tid;
             int sk = -1;
             for (int k = 0; k < 2; ++k) {
@@ -459,6 +467,17 @@ __global__ __launch_bounds__(kFusedWG) void k_frontier_summary(
         }
         __syncthreads();  // the LDS tables are cleared for the next window
     }
+}
+
+template <int VEC>
+const void* pick_fused(int R)
+{
+    if (R <= 8) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 4>);
+    if (R <= 16) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 8>);
+    if (R <= 32) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 16>);
+    if (R <= 64) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 2, 32>);
+    if (R <= 128) return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 4, 32>);
+    return reinterpret_cast<const void*>(&k_frontier_summary<VEC, 8, 32>);  // R <= kFusedMaxR
 }
 
 // Exposed time led: the same segmented histogram as k_window_counts, with
@@ -869,12 +888,9 @@ SF_API int sf_frontier_summary(const int64_t* durations, int64_t T, int32_t R, i
     for (int a = 0; a < 6; ++a)
         for (int b = a + 1; b < 6; ++b)
             if (!disjoint(bufs[a], sizes[a], bufs[b], sizes[b])) return SF_EINVAL;
-    const int64_t n_max = window < T ? window : T;
-    if (R <= kFusedMaxR && S <= kFusedMaxS && n_max <= kFusedMaxWindow &&
-        T * S * (int64_t)R <= kFusedMaxSamples) {
+    if (fused_fits(T, R, S, window)) {
         const bool vec2 = (R % 2 == 0) && aligned(durations, 16);
-        const void* fn = vec2 ? reinterpret_cast<const void*>(&k_frontier_summary<2, 2, 4>)
-                              : reinterpret_cast<const void*>(&k_frontier_summary<1, 2, 4>);
+        const void* fn = vec2 ? pick_fused<2>(R) : pick_fused<1>(R);
         int Ri = R, Si = S;
         int64_t Wl = W;
         void* args[] = {(void*)&durations,         (void*)&T,               (void*)&Ri,

@@ -489,6 +489,16 @@ def test_window_whole_ends(sf, R, S, T, window):
     test_window_whole_edges(sf, R, S, T, window)
 
 
+@pytest.mark.parametrize("R,S,T,window", [
+    (9, 4, 320, 160), (9, 4, 322, 161), (16, 5, 300, 128), (15, 12, 150, 53), (16, 12, 150, 54), (31, 12, 100, 25),
+    (32, 12, 100, 26), (64, 6, 60, 20), (63, 6, 60, 21), (65, 8, 30, 10), (129, 1, 160, 80), (255, 8, 33, 10),
+    (256, 8, 30, 11), (257, 8, 30, 10), (8, 12, 340, 170), (7, 12, 342, 171), (8, 13, 90, 30), (5, 8, 512, 256)])
+def test_fused_summary_ends(sf, R, S, T, window):
+    """Both sides of the limits of the one-launch summary: windows of one and
+    two rounds of steps, one and several chunks of rows, odd rank counts."""
+    test_window_whole_edges(sf, R, S, T, window)
+
+
 def test_lead_exposed_ties_signs_and_out_of_range_leaders(sf):
     """Stage-total ties, rank ties on exposed time, zero rows (rank -1),
     negative advances (never a suspect) and leaders outside [0, R)."""

@@ -111,3 +111,12 @@ def test_window_sum_of_short_windows_is_not_unrolled(recorder):
 def test_whole_windows(recorder, call, R, S, T, window, whole):
     """One workgroup per window where that is the faster way."""
     assert kernels(recorder, call, R, S, T, window)[0].startswith("k_window_whole") == whole
+
+@pytest.mark.parametrize("R,S,window,fused", [
+    (8, 6, 100, True), (8, 12, 100, True), (8, 12, 200, False), (16, 6, 100, True), (16, 6, 200, False), (32, 6, 50, True),
+    (32, 6, 100, False), (64, 4, 20, True), (64, 8, 1, True), (64, 6, 50, False), (256, 4, 20, True), (256, 6, 50, False),
+    (200, 8, 1, True), (257, 1, 1, False), (8, 13, 10, False)])
+def test_fused_summary(recorder, R, S, window, fused):
+    """The one-launch summary takes windows of about one round of steps, at up
+    to 256 ranks."""
+    assert kernels(recorder, "sf_frontier_summary", R, S, 10 * window, window)[0].startswith("k_frontier_summary") == fused
