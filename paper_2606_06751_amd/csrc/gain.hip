@@ -20,6 +20,8 @@
 #include "sf_host.h"
 #include "sf_select.h"
 
+#include <type_traits>
+
 namespace sfk {
 
 template <int K, int G, int WG, int SMAX, bool RUN>
@@ -27,11 +29,12 @@ __global__ __launch_bounds__(WG) void k_exposure_gain(
     const int64_t* __restrict__ d, const int64_t* __restrict__ btilde, int64_t T, int R, int S,
     int64_t window, int64_t* __restrict__ gain, int64_t* __restrict__ makespan)
 {
-    static_assert(K % 2 == 0 && (WG % G == 0 || G == WG), "shape");
+    static_assert((K == 1 || K % 2 == 0) && (WG % G == 0 || G == WG), "shape");
+    constexpr int VEC = K == 1 ? 1 : 2;
     constexpr int SUB = G < 64 ? G : 64;
     constexpr int SPW = WG / G;
     constexpr int SPS = G / SUB;
-    constexpr int NLD = K / 2;
+    constexpr int NLD = K / VEC;
     constexpr int RT = G * K;
     constexpr int NCOL = SMAX + 1;  // SMAX replaced-stage maxima, then F
     static_assert(!RUN || SMAX <= 16, "running maxima of up to 16 stages");
@@ -58,8 +61,8 @@ __global__ __launch_bounds__(WG) void k_exposure_gain(
                 // R >= 2: with odd R the last pair overlaps the one before;
                 // a pair past R re-reads the tile's first ranks (the last
                 // pair instead ran 20% slower at 64 ranks)
-                const int r = r0 + (l * G + gl) * 2;
-                idx[l] = min(r < R ? r : r0, R - 2);
+                const int r = r0 + (l * G + gl) * VEC;
+                idx[l] = min(r < R ? r : r0, R - VEC);
             }
             int64_t tot[K];
             int64_t dl[K][SMAX];
@@ -67,28 +70,53 @@ __global__ __launch_bounds__(WG) void k_exposure_gain(
             for (int k = 0; k < K; ++k) tot[k] = 0;
             // the tile's loads all in flight before any is used: left to the
             // compiler, it waits for the first ones in between to save
-            // registers (64 ranks x 6 stages: 237 us against 187 per 0.8 GB;
-            // with 12 stages or running maxima it is 2-3% faster that way)
-            v2i64_a8 x[SMAX][NLD], y[SMAX][NLD];
+            // registers (64 ranks x 6 stages: 237 us against 187 per 0.8 GB).
+            // With running maxima (a step's tiles in series) the durations
+            // come first, then the baseline: both at once took 108 us against
+            // 88 for 32768 ranks x 6 x 100 and 237 against 208 for 45000 x 12 x
+            // 100
+            constexpr bool TWO = RUN && SMAX >= 6;
+            typedef typename std::conditional<VEC == 2, v2i64_a8, int64_t>::type L;
+            L x[SMAX][NLD], y[SMAX][NLD];
+            auto at = [](const L& v, int e) {
+                if constexpr (VEC == 2) return v[e];
+                else return v;
+            };
 #pragma unroll
             for (int s = 0; s < SMAX; ++s) {
                 const int sr = s < S ? s : 0;
 #pragma unroll
                 for (int l = 0; l < NLD; ++l) {
-                    x[s][l] = __builtin_nontemporal_load(reinterpret_cast<const v2i64_a8*>(dt + (int64_t)sr * R + idx[l]));
-                    y[s][l] = *reinterpret_cast<const v2i64_a8*>(bw + (int64_t)sr * R + idx[l]);
+                    x[s][l] = __builtin_nontemporal_load(reinterpret_cast<const L*>(dt + (int64_t)sr * R + idx[l]));
+                    if (!TWO) y[s][l] = *reinterpret_cast<const L*>(bw + (int64_t)sr * R + idx[l]);
                 }
             }
             if (SMAX <= 8 && !RUN) __builtin_amdgcn_sched_barrier(0);
+            if (TWO) {
+#pragma unroll
+                for (int l = 0; l < NLD; ++l)
+#pragma unroll
+                    for (int s = 0; s < SMAX; ++s)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e)
+                            if (s < S) tot[l * VEC + e] += at(x[s][l], e);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < SMAX; ++s) {
+                    const int sr = s < S ? s : 0;
+#pragma unroll
+                    for (int l = 0; l < NLD; ++l) y[s][l] = *reinterpret_cast<const L*>(bw + (int64_t)sr * R + idx[l]);
+                }
+            }
 #pragma unroll
             for (int s = 0; s < SMAX; ++s) {
 #pragma unroll
                 for (int l = 0; l < NLD; ++l) {
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const int64_t red = x[s][l][e] - y[s][l][e];
-                        dl[l * 2 + e][s] = red > 0 ? red : 0;
-                        if (s < S) tot[l * 2 + e] += x[s][l][e];
+                    for (int e = 0; e < VEC; ++e) {
+                        const int64_t red = at(x[s][l], e) - at(y[s][l], e);
+                        dl[l * VEC + e][s] = red > 0 ? red : 0;
+                        if (!TWO && s < S) tot[l * VEC + e] += at(x[s][l], e);
                     }
                 }
             }
