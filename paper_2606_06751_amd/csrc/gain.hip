@@ -574,6 +574,7 @@ GainVariant pick_gain_g(int R)
 // and holds its deltas, so 12 stages under SMAX = 16 ran 14-18% slower than
 // under SMAX = 12 (and 6 under 8, 9% slower) on MI355X.
 constexpr int kGainRegS = 24;  // stages whose deltas k_exposure_gain keeps in registers
+constexpr int kGainMaxS = 64;  // the same where k_exposure_gain_near does not reach
 
 GainVariant pick_gain(int R, int S)
 {
@@ -582,7 +583,9 @@ GainVariant pick_gain(int R, int S)
     if (S <= 8) return pick_gain_g<8>(R);
     if (S <= 12) return pick_gain_g<12>(R);
     if (S <= 16) return pick_gain_g<16>(R);
-    return pick_gain_g<24>(R);  // S <= kGainRegS
+    if (S <= 24) return pick_gain_g<24>(R);
+    if (S <= 32) return gain_variant<2, 256, 256, 32>();
+    return gain_variant<1, 256, 256, 64>();  // S <= kGainMaxS
 }
 
 template <int WG, int KP, int NS = 1>
@@ -653,10 +656,13 @@ bool use_near(int64_t T, int R, int S)
 // handful of ranks (8 ranks x 6 stages 66 : 88, x 12 157 : 166, x 24 322 :
 // 442), 13 and more stages from 33 to 64 ranks (48 x 16 227 : 287), more
 // stages than the registers hold, and 17 to 24 of them where its lanes would
-// idle (16 ranks x 20 302 : 324, 48 x 24 236 : 382; 32 x 20 261 : 200).
+// idle (16 ranks x 20 302 : 324, 48 x 24 236 : 382; 32 x 20 261 : 200).  Past
+// kNearMaxR ranks the registers hold up to 64 stages (45000 ranks x 100 steps: 25
+// stages 700 us against 5000, 64 x 32 3200 against 12000).
 bool use_wide(int R, int S)
 {
-    if (R <= 8 || S > kGainRegS) return true;
+    if (R <= 8 || S > (R > kNearMaxR ? kGainMaxS : kGainRegS)) return true;
+    if (R > kNearMaxR) return false;
     if (S >= 17) return R <= 16 || (R > 32 && R <= 128);
     return S >= 13 && R > 32 && R <= 64;
 }

@@ -953,6 +953,14 @@ def test_gain_near_edges(sf, R, S, T):
     print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
     assert_gain_equal(sf, d, bt, 7)
 
+@pytest.mark.parametrize("R,S,T", [(32769, 25, 2), (32770, 32, 2), (32771, 33, 2), (40001, 64, 1), (32769, 65, 1),
+                                   (32769, 9, 3), (33001, 16, 2), (50000, 7, 3), (16385, 6, 9), (16385, 7, 65), (5001, 5, 3),
+                                   (8193, 3, 9), (4097, 4, 8), (4097, 4, 9), (16384, 2, 3)])
+def test_gain_shape_ends(sf, R, S, T):
+    """Past the ranks of the near-frontier pass, and few steps of many ranks,
+    on both sides of the rules."""
+    test_gain_near_edges(sf, R, S, T)
+
 
 def test_gain_golden_cases(sf):
     import pins

@@ -120,3 +120,12 @@ def test_fused_summary(recorder, R, S, window, fused):
     """The one-launch summary takes windows of about one round of steps, at up
     to 256 ranks."""
     assert kernels(recorder, "sf_frontier_summary", R, S, 10 * window, window)[0].startswith("k_frontier_summary") == fused
+
+
+@pytest.mark.parametrize("R,S,kernel", [
+    (32769, 25, "k_exposure_gain<2, 256, 256, 32"), (65536, 32, "k_exposure_gain<2, 256, 256, 32"),
+    (45000, 33, "k_exposure_gain<1, 256, 256, 64"), (32769, 64, "k_exposure_gain<1, 256, 256, 64"),
+    (32769, 65, "k_exposure_gain_wide"), (32768, 25, "k_exposure_gain_near"), (20, 25, "k_exposure_gain_wide")])
+def test_gain_of_many_stages(recorder, R, S, kernel):
+    """Up to 64 stages in registers past the ranks of the near-frontier pass."""
+    assert kernels(recorder, "sf_exposure_gain", R, S, 20, 10)[0].startswith(kernel)
