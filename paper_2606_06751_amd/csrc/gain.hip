@@ -640,16 +640,26 @@ GainVariant pick_near(int64_t T, int R)
 // part of the step and its replacement often takes the row passes (16384
 // ranks: 175 against 145; with 12 stages 130 against 149).
 //   9 stages and more: past 128 ranks (12 stages: 200 ranks 141 : 237, 1024
-//     130 : 147, 4096 127 : 136; 128 ranks 191 : 130);
-//   7 and 8: from 129 to 4096 ranks (8 stages: 200 ranks 183 : 237, 4096
-//     133 : 134, 8192 148 : 134);
+//     130 : 147, 4096 127 : 136; 128 ranks 191 : 130); past 16384 ranks, one
+//     workgroup per CU, 13 stages, or 9 up to 256 steps (24576 x 12: 100 steps
+//     66 : 121, 600 272 : 280, synchronised 347 : 280);
+//   7 and 8: from 129 to 2048 ranks, to 4096 up to 512 steps (8 stages: 200
+//     ranks 183 : 237, 2048 x 4000 90 : 91, 4096 x 1000 53 : 50, synchronised 61 : 50);
 //   17 and more: wherever a step holds 1600 samples (20 stages x 96 ranks
-//     190 : 229, 32 x 64 211 : 245, 32 x 48 259 : 245, 132 x 1024 153 : 640).
+//     190 : 229, 32 x 64 211 : 245, 32 x 48 259 : 245, 132 x 1024 153 : 640);
+//   few steps past 4096 ranks, where the other kernels give a step 256 threads:
+//     up to 256 steps with 5 stages, or past 8192 ranks (16384 x 5: one step 15 :
+//     36, 100 33 : 48, 400 72 : 70; 8192 x 4 x 64 19 : 21); past 16384 ranks up to 8
+//     steps, or 64 with 7 stages (32768 x 8: 8 steps 53 : 102, 64 58 : 107, 150 82 :
+//     112, synchronised 105 : 112; x 5: 8 56 : 74, 64 67 : 82, synchronised 150 steps
+//     83 : 85).
 bool use_near(int64_t T, int R, int S)
 {
     if (R > kNearMaxR || S > kNearMaxS || T > INT32_MAX) return false;
     if (S >= 17 && R >= 48 && R * S >= 1600) return true;
-    return R > 128 && (S >= 9 || (S >= 7 && R <= 4096));
+    if (R > 16384) return S >= 13 || T <= (S >= 9 ? 256 : S >= 7 ? 64 : 8);
+    if (R > 4096 && T <= 256 && (S >= 5 || R > 8192 || T <= 8)) return true;
+    return R > 128 && (S >= 9 || (S >= 7 && R <= (T <= kNearFewSteps ? 4096 : 2048)));
 }
 
 // Where the two-pass kernel beats the one with the deltas in registers: a

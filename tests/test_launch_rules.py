@@ -129,3 +129,14 @@ def test_fused_summary(recorder, R, S, window, fused):
 def test_gain_of_many_stages(recorder, R, S, kernel):
     """Up to 64 stages in registers past the ranks of the near-frontier pass."""
     assert kernels(recorder, "sf_exposure_gain", R, S, 20, 10)[0].startswith(kernel)
+
+
+@pytest.mark.parametrize("R,S,T,near", [
+    (16384, 5, 1, True), (16384, 5, 256, True), (16384, 5, 257, False), (8192, 4, 8, True), (8192, 4, 9, False),
+    (8194, 4, 64, True), (32768, 5, 8, True), (32768, 5, 9, False), (32768, 8, 64, True), (32768, 8, 65, False),
+    (24576, 12, 256, True), (24576, 12, 257, False), (24576, 13, 1000, True), (4096, 8, 512, True), (4096, 8, 513, False),
+    (2048, 8, 4000, True), (4096, 9, 4000, True)])
+def test_gain_of_few_steps(recorder, R, S, T, near):
+    """The near-frontier pass, a whole workgroup per step, where few steps leave
+    the other kernels' chip idle, and not where it lost to them."""
+    assert kernels(recorder, "sf_exposure_gain", R, S, T, 50)[0].startswith("k_exposure_gain_near") == near
