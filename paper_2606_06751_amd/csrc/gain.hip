@@ -274,12 +274,18 @@ __global__ __launch_bounds__(WG) void k_exposure_gain_wide(
 //     baseline: F - delta is a first candidate maximum of every stage, L the
 //     smallest of them;
 //  2. reads durations and baseline of the ranks with P_r > L (a handful as a
-//     rule), for the stages whose candidate they can still raise.
-// When more than kNearCap ranks lie above L (some stage's replacement drops
-// the top rank far), the waves' own top ranks are tried first, which raises L
-// when it was the top rank alone; then the stage of the smallest candidate is
-// resolved over all ranks from its two rows, which leaves L to the others, up
-// to kNearRows times; then all stages are.  The result is the same maximum in
+//     rule), for the stages whose candidate they can still raise, adjacent
+//     lanes on adjacent ranks of a stage.
+// When half of the ranks or more than kNearCap lie above L (some stage's
+// replacement drops the top rank far, or a collective has made the totals
+// equal), the waves' own top ranks and the first kNearFirst of the list are
+// tried first: that raises L where it was the top rank alone, and among equal
+// totals a few ranks settle nearly every stage, where reading all of them cost
+// more than the kernel saves (512 ranks x 8 x 4000 steps synchronised before
+// the last stages 39 -> 31 us, 29 without the kernel; 1024 x 24 x 1000 with equal
+// totals 59 -> 34, 52).  Then the stage of the smallest candidate is resolved
+// over all ranks from its two rows, which leaves L to the others, up to
+// kNearRows times; then all stages are.  The result is the same maximum in
 // each case.  Pairs past R read 0 (they lie past the stage row's buffer
 // resource), and a total of 0 never exceeds L >= 0; with odd R the last pair
 // overlaps the one before.
@@ -289,8 +295,11 @@ __global__ __launch_bounds__(WG) void k_exposure_gain_wide(
 // kernels that took these shapes before; 12000 x 12 x 2777 535 -> 489 us and
 // 16384 x 12 x 2034 492 -> 483 us against a radix search over the totals for
 // a bound with at least 32 ranks above it (which also needed a barrier per
-// stage row to run well).
+// stage row to run well).  The shape past 16384 ranks holds 32 totals per lane
+// and spills 56 VGPRs around the list's construction (two loads in flight
+// instead of four spill the same and run 5-10% slower).
 constexpr int kNearCap = 512;
+constexpr int kNearFirst = 32;  // at most kNearCap: entries of the list
 constexpr int kNearMaxR = 32768;
 constexpr int64_t kNearFewSteps = 512;
 constexpr int kNearMaxS = 4096;  // stages whose candidates fit in LDS (32 KB)
@@ -430,8 +439,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
             for (int j = 0; j < 4; ++j) {
                 const uint32_t i = i0 + (uint32_t)(j * WG);
                 const uint32_t ii = i < np ? i : 0u;
-                const uint32_t q = ii / (uint32_t)S;
-                const int s = (int)(ii - q * (uint32_t)S);
+                const uint32_t sq = ii / n, q = ii - sq * n;
+                const int s = (int)sq;
                 tq[j] = tots[q];
                 sj[j] = s;
                 need[j] = i < np && tq[j] > cand[s];  // cand only grows: a stale read is safe
@@ -514,13 +523,15 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
         }
         __syncthreads();
         const uint32_t nq = q_n;
-        if (nq <= (uint32_t)kNearCap) {
+        const int at_once = round == 0 && R < 2 * kNearCap ? max(kNearFirst, R / 2) : kNearCap;
+        if (nq <= (uint32_t)at_once) {
             fold(q_rank, q_tot, nq);
             break;
         }
         const int s_low = __builtin_amdgcn_readfirstlane((int)(key & ((1u << kNearSBits) - 1u)));
         if (round == 0) {
             fold(w_rank, w_tot, NW);
+            fold(q_rank, q_tot, kNearFirst);
         } else if (round <= kNearRows) {
             if (slice == 0) row(s_low);
         } else {

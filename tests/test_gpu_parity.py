@@ -953,6 +953,25 @@ def test_gain_near_edges(sf, R, S, T):
     print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
     assert_gain_equal(sf, d, bt, 7)
 
+@pytest.mark.parametrize("R,S,T", [(3, 20, 40), (60, 30, 20), (130, 9, 40), (201, 8, 520), (384, 12, 30), (513, 7, 30),
+                                   (1023, 9, 530), (1024, 24, 6), (2049, 12, 6), (9000, 9, 4), (20001, 10, 3)])
+def test_gain_equalised_totals(sf, R, S, T):
+    """Totals that a collective has made equal, where most ranks lie above
+    the first bound: all equal, equal up to the jitter of the last stage, and
+    equal but for half of the ranks; baselines above, below and around the
+    durations."""
+    rng = np.random.Generator(np.random.PCG64(R * 7 + S))
+    d = rng.integers(900, 1100, size=(T, S, R), dtype=np.int64)
+    total = d.sum(axis=1)
+    d[:, S // 2] += total.max(axis=1, keepdims=True) - total
+    d[1::4, S - 1] += rng.integers(0, 50, size=d[1::4, S - 1].shape)
+    d[2::4, 0, : R // 2] -= 300
+    bt = np.full((-(-T // 9), S, R), 1000, dtype=np.int64)
+    bt[:, 1::3] = 5000
+    bt[:, 2::5] = rng.integers(0, 1100, size=bt[:, 2::5].shape)
+    print("case R=%d S=%d T=%d" % (R, S, T), flush=True)
+    assert_gain_equal(sf, d, bt, 9)
+
 @pytest.mark.parametrize("R,S,T", [(32769, 25, 2), (32770, 32, 2), (32771, 33, 2), (40001, 64, 1), (32769, 65, 1),
                                    (32769, 9, 3), (33001, 16, 2), (50000, 7, 3), (16385, 6, 9), (16385, 7, 65), (5001, 5, 3),
                                    (8193, 3, 9), (4097, 4, 8), (4097, 4, 9), (16384, 2, 3)])
