@@ -523,7 +523,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(4))) void k_
         }
         __syncthreads();
         const uint32_t nq = q_n;
-        const int at_once = round == 0 && R < 2 * kNearCap ? max(kNearFirst, R / 2) : kNearCap;
+        // (a workgroup of 1024 for so few ranks has few steps, and a round
+        // costs it more than the reads)
+        const int at_once = round == 0 && WG < 1024 && R < 2 * kNearCap ? max(kNearFirst, R / 2) : kNearCap;
         if (nq <= (uint32_t)at_once) {
             fold(q_rank, q_tot, nq);
             break;
@@ -625,10 +627,11 @@ GainVariant pick_wide(int R)
 // in the 1024-thread shapes).  From 4097 to 8192 ranks 512 threads x 8 pairs
 // beat 1024 x 4 by 5-40%.  With few steps the
 // stages of one are split over the waves of a wide workgroup, since there are
-// not enough workgroups to fill the chip.
+// not enough workgroups to fill the chip: up to 1024 ranks while every step has
+// a CU to itself (384 ranks x 8: 256 steps 10.4 us, 300 12.0 against 9.1).
 GainVariant pick_near(int64_t T, int R)
 {
-    if (T <= kNearFewSteps) {
+    if (T <= (R <= 1024 ? 256 : kNearFewSteps)) {
         if (R <= 256) return near_variant<1024, 1, 8>();
         if (R <= 512) return near_variant<1024, 1, 4>();
         if (R <= 1024) return near_variant<1024, 1, 2>();

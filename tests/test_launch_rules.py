@@ -140,3 +140,10 @@ def test_gain_of_few_steps(recorder, R, S, T, near):
     """The near-frontier pass, a whole workgroup per step, where few steps leave
     the other kernels' chip idle, and not where it lost to them."""
     assert kernels(recorder, "sf_exposure_gain", R, S, T, 50)[0].startswith("k_exposure_gain_near") == near
+
+
+@pytest.mark.parametrize("R,T,shape", [(200, 256, "1024, 1, 8"), (200, 257, "256, 1, 2"), (512, 257, "256, 1, 1"),
+                                       (1024, 256, "1024, 1, 2"), (1024, 257, "256, 2, 1"), (2048, 512, "1024, 1, 1"),
+                                       (2048, 513, "256, 4, 1")])
+def test_gain_wide_workgroups_for_few_steps(recorder, R, T, shape):
+    assert ", ".join(template_args(kernels(recorder, "sf_exposure_gain", R, 12, T, 50)[0])) == shape
