@@ -290,9 +290,8 @@ int sf_rank_spread(const int64_t* durations, int64_t T, int32_t R, int32_t S,
  *   T, R, S     0 <= T, 1 <= R <= SF_MAX_R, 1 <= S.  T == 0 is a no-op.
  *   window      steps per window, >= 1 (windows as for sf_window_summary).
  *               Windows of up to 4096 steps are held on chip in tiles of
- *               (stage, rank) columns; longer ones, and medians of 2^32 ns
- *               and above, are selected from global memory, one column at a
- *               time (slower, same results).
+ *               (stage, rank) columns; longer ones are selected from global
+ *               memory, one column at a time (slower, same results).
  *   out_median  [W][S][R] int64 ns.
  *   stream      HIP stream.
  *

@@ -23,13 +23,19 @@
 // takes 94-97% of its time up to 512 steps).  Measured on MI355X, 4096 ranks
 // x 12 stages x 5000 steps: windows of 250 steps 535 -> 350 us, of 100 steps
 // 1073 -> 340 us against the former per-column radix select with LDS
-// histograms; 256 x 6 x 40000, windows of 2000: 2540 -> 150 us (the former
+// histograms; 256 x 6 x 40000, windows of 2000: 2540 -> 110 us (the former
 // kernel streamed each column there).
 //
-// Values of 2^32 and above saturate in the tile; a column whose median
-// saturates is selected again in 64 bits, streamed from global memory by its
-// wave (wave_select_stream).  Windows longer than the tile rows, and a
-// single column, take that streaming select for every column.
+// A tile with a value of 2^32 or above is resolved twice: by the high halves,
+// while the values are still in registers, then by the low halves of the
+// candidates left.  Nothing overlaps its first select, but the time still does
+// not depend on how many columns are such ones: with one stage of 6 s, 4096 x 12
+// x 1000, windows of 250 79 us (73 without; 228 for the former kernel, 450 where
+// a saturated column was streamed from global memory by its wave), 58 x 6 x 2000,
+// windows of 50 10 (11, 45).
+//
+// Windows longer than the tile rows, and a single column, are streamed from
+// global memory column by column (wave_select_stream).
 
 #include "sf_device.h"
 #include "sf_host.h"
@@ -130,7 +136,6 @@ __device__ u64 wave_select_stream(Get get, int64_t n, uint32_t* h, int lane)
 }
 
 constexpr int kMedWG = 512;
-constexpr int kMedWaves = kMedWG / 64;
 constexpr int64_t kMedTileRows = 4096;  // longest window of the tiled kernel
 
 // Sum over aligned groups of N lanes (a power of two), in every lane of the
@@ -225,7 +230,7 @@ __global__ __launch_bounds__(kMedWG) __attribute__((amdgpu_waves_per_eu(W == 1 ?
     constexpr int CPW = 64 / PARTS;          // columns per wave
     static_assert(PARTS >= 2 && PARTS <= 64 && NSW == 16 * W, "shape");
     __shared__ __attribute__((aligned(16))) uint32_t tile[ROWS * STRIDE];
-    __shared__ __attribute__((aligned(16))) uint32_t hist[kMedWaves][kSelWords];
+    __shared__ uint32_t wide_sh;  // some value of the tile has a high word
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -234,8 +239,7 @@ __global__ __launch_bounds__(kMedWG) __attribute__((amdgpu_waves_per_eu(W == 1 ?
     const int c = (tid % TPR) * 2;   // its column pair within a tile row
     const int part = lane % PARTS;
     const int col = wave * CPW + lane / PARTS;  // the column it selects in
-    uint32_t* h = hist[wave];
-    for (int i = lane; i < kSelWords; i += 64) h[i] = 0;  // cleared again by every scan
+    if (tid == 0) wide_sh = 0;
 
     // the workgroups in flight take adjacent tiles, an XCD's side by side, so
     // that neighbouring pieces of a row are read together (measured against a
@@ -279,64 +283,59 @@ __global__ __launch_bounds__(kMedWG) __attribute__((amdgpu_waves_per_eu(W == 1 ?
         const int n = rows_of(w);
         const int64_t c0 = min(k0 * COLS, C - 2);
         __syncthreads();  // every wave has taken the previous tile's columns
+        uint32_t* const at = tile + i0 * STRIDE + (int)(min(c0 + c, C - 2) - c0);
+        auto put = [&](bool high) {  // the tile's words: the values' low or high halves
+            if (STRIDE % 2 == 0 && (C & 1) == 0) {
+                // pairs at even words: one 8-byte store each
+#pragma unroll
+                for (int j = 0; j < NSW; ++j)
+                    *reinterpret_cast<uint2*>(__builtin_assume_aligned(at + j * RPS * STRIDE, 8)) =
+                        high ? make_uint2((uint32_t)((u64)x[j].x >> 32), (uint32_t)((u64)x[j].y >> 32))
+                             : make_uint2((uint32_t)x[j].x, (uint32_t)x[j].y);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NSW; ++j) {
+                    at[j * RPS * STRIDE] = high ? (uint32_t)((u64)x[j].x >> 32) : (uint32_t)x[j].x;
+                    at[j * RPS * STRIDE + 1] = high ? (uint32_t)((u64)x[j].y >> 32) : (uint32_t)x[j].y;
+                }
+            }
+        };
+        put(false);
         uint32_t hiw = 0;
 #pragma unroll
         for (int j = 0; j < NSW; ++j) hiw |= (uint32_t)((u64)x[j].x >> 32) | (uint32_t)((u64)x[j].y >> 32);
-        if (__ballot(hiw != 0) != 0) {
-            // values past 32 bits saturate; a median that does is selected
-            // again in 64 bits below
-#pragma unroll
-            for (int j = 0; j < NSW; ++j) {
-                if ((u64)x[j].x >> 32) x[j].x = 0xFFFFFFFFll;
-                if ((u64)x[j].y >> 32) x[j].y = 0xFFFFFFFFll;
-            }
-        }
-        uint32_t* const at = tile + i0 * STRIDE + (int)(min(c0 + c, C - 2) - c0);
-        if (STRIDE % 2 == 0 && (C & 1) == 0) {
-            // pairs at even words: one 8-byte store each
-#pragma unroll
-            for (int j = 0; j < NSW; ++j)
-                *reinterpret_cast<uint2*>(__builtin_assume_aligned(at + j * RPS * STRIDE, 8)) =
-                    make_uint2((uint32_t)x[j].x, (uint32_t)x[j].y);
-        } else {
-#pragma unroll
-            for (int j = 0; j < NSW; ++j) {
-                at[j * RPS * STRIDE] = (uint32_t)x[j].x;
-                at[j * RPS * STRIDE + 1] = (uint32_t)x[j].y;
-            }
-        }
+        if (__ballot(hiw != 0) != 0 && lane == 0) wide_sh = 1;
         __syncthreads();
+        const bool wide = wide_sh != 0;  // uniform over the workgroup
         const int64_t wc = w;
         id += nslot;
         const bool more = id < tiles;
-        if (more) {
-            w += dw;
-            k0 += dk;
-            if (k0 >= nchunk) {
-                k0 -= nchunk;
-                ++w;
-            }
-            load(w, min(k0 * COLS, C - 2));  // flies while this tile is resolved
-        }
-        // the lane's 32 W values (slots part, part + PARTS, ...): the mask m
-        // of those within the window, and the bits below top of their OR
-        uint32_t m[W];
         const uint32_t* base = tile + part * STRIDE + col;
         const bool live = c0 + col < C;
+        // the lane's 32 W values (slots part, part + PARTS, ...): the mask m
+        // of those that are candidates, at first those within the window, of
+        // which the median has rank kk
+        uint32_t m[W];
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const int nv = (n - part + PARTS - 1) / PARTS - q * 32;  // slots of this word below n
+            m[q] = nv >= 32 ? 0xFFFFFFFFu : (nv <= 0 ? 0u : (1u << nv) - 1u);
+        }
+        uint32_t kk = (uint32_t)((n - 1) / 2);
+        // the candidates' median in the tile's words; fewer are left in m
+        auto select = [&]() {
+        // the bits below the top one of the columns' OR
         int nbits;
         {
             uint32_t vor = 0;
 #pragma unroll
             for (int q = 0; q < W; ++q) {
-                const int nv = (n - part + PARTS - 1) / PARTS - q * 32;  // slots of this word below n
-                m[q] = nv >= 32 ? 0xFFFFFFFFu : (nv <= 0 ? 0u : (1u << nv) - 1u);
 #pragma unroll
                 for (int k = 0; k < 32; ++k) vor |= base[(q * 32 + k) * PARTS * STRIDE];
             }
             vor = wave_or32(vor);
             nbits = vor ? 32 - __builtin_clz(vor) : 0;
         }
-        uint32_t kk = (uint32_t)((n - 1) / 2);
         int sh = nbits > 16 ? nbits - 16 : 0;
         for (;;) {
             // bits [sh, sh + 16) of the values as planes; in a second round
@@ -390,17 +389,32 @@ __global__ __launch_bounds__(kMedWG) __attribute__((amdgpu_waves_per_eu(W == 1 ?
 #pragma unroll
         for (int q = 0; q < W; ++q)
             if (m[q]) res = base[(q * 32 + __builtin_ctz(m[q])) * PARTS * STRIDE];
-        res = group_max_all32<PARTS>(res);
-        int64_t* const mrow = med + wc * C + c0;
-        const bool mine = part == 0 && live;
-        if (mine && res != 0xFFFFFFFFu) mrow[col] = (int64_t)res;
-        // medians of 2^32 - 1 and above: the wave streams the column
-        for (u64 wide = __ballot(mine && res == 0xFFFFFFFFu); wide != 0; wide &= wide - 1) {
-            const int j = wave * CPW + (int)__builtin_ctzll(wide) / PARTS;
-            const int64_t* q = d + wc * window * C + c0 + j;
-            const u64 r = wave_select_stream([&](int64_t i) { return (u64)q[i * C]; }, n, h, lane);
-            if (lane == 0) mrow[j] = (int64_t)r;
+        return group_max_all32<PARTS>(res);
+        };
+        uint32_t high = 0;
+        if (wide) {
+            // the high halves first (the values are still in x), then the low
+            // ones of the candidates that are left
+            __syncthreads();  // every wave has read wide_sh
+            put(true);
+            if (tid == 0) wide_sh = 0;
+            __syncthreads();
+            high = select();
+            __syncthreads();
+            put(false);
+            __syncthreads();
         }
+        if (more) {
+            w += dw;
+            k0 += dk;
+            if (k0 >= nchunk) {
+                k0 -= nchunk;
+                ++w;
+            }
+            load(w, min(k0 * COLS, C - 2));  // flies while this tile is resolved
+        }
+        const uint32_t res = select();
+        if (part == 0 && live) med[wc * C + c0 + col] = (int64_t)(((u64)high << 32) | res);
         if (!more) break;
     }
 }

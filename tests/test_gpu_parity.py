@@ -1529,3 +1529,23 @@ def test_window_sums_of_gain_and_spread(sf, window):
     print("case window=%d" % window, flush=True)
     assert_gain_equal(sf, d, bt, window)
     assert_spread_equal(sf, d, window)
+
+
+@pytest.mark.parametrize("S,R,T,window", [(3, 1401, 2300, 1100), (1, 2103, 4300, 2100), (5, 211, 4096, 4096),
+                                          (7, 1001, 700, 50), (3, 1401, 1300, 130), (3, 1402, 1900, 500),
+                                          (1, 9001, 1500, 600)])
+def test_median_many_tiles(sf, S, R, T, window):
+    """More tiles than workgroups in every shape, so that tiles follow each
+    other in LDS while the next one's loads are in flight; a ragged last
+    window, and values of 2^32 and above in some tiles: medians on both sides
+    of 2^32, equal high halves, high halves that differ, one far value."""
+    rng = np.random.Generator(np.random.PCG64(window + R))
+    d = (4e7 * np.exp(0.1 * rng.standard_normal((T, S, R), dtype=np.float32))).astype(np.int64)
+    d[:, 0, 10:40] += 1 << 32
+    d[:, S - 1, 50:53] = rng.integers(0, 1 << 47, size=(T, 3))
+    d[:, S // 2, 100:110] = (1 << 32) - 2 + rng.integers(0, 4, size=(T, 10))
+    d[T // 2, 0, 60] = 1 << 46
+    d[-(T % window or window):, S - 1, R - 9:] += 5 << 32
+    d[:window, 0, R - 1] = (3 << 33) + rng.integers(0, 3, size=window)
+    print("case S=%d R=%d T=%d window=%d" % (S, R, T, window), flush=True)
+    assert_median_equal(sf, d, window)
