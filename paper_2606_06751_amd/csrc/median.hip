@@ -257,13 +257,13 @@ __global__ __launch_bounds__(kMedWG) __attribute__((amdgpu_waves_per_eu(W == 1 ?
     auto load = [&](int64_t w, int64_t c0) {
         const int n = rows_of(w);
         const int64_t cc = c0 + c < C - 2 ? c0 + c : C - 2;
-        // the wave's rows of a sweep through a buffer resource that ends
-        // after row n - 1: slots past the window read 0 without a branch or
-        // memory traffic
-        const char* q = reinterpret_cast<const char*>(d + (w * window + wrow) * C);
-        const uint32_t off = (uint32_t)(((i0 - wrow) * C + cc) * 8);  // below 2^32: the host checks
+        // the wave's rows of a sweep, from the tile's first column on, through
+        // a buffer resource that ends after row n - 1: slots past the window
+        // read 0 without a branch or memory traffic
+        const char* q = reinterpret_cast<const char*>(d + (w * window + wrow) * C + c0);
+        const uint32_t off = (uint32_t)(((i0 - wrow) * C + cc - c0) * 8);  // below 2^32: the host checks
         const int64_t step = (int64_t)RPS * C * 8;
-        int64_t left = (n - wrow) * C * 8;
+        int64_t left = ((n - wrow) * C - c0) * 8;
 #pragma unroll
         for (int j = 0; j < NSW; ++j) {
             const int over = (int)(left >> 32);  // compared by halves: the scalar unit has no 64-bit order
@@ -452,13 +452,16 @@ __global__ __launch_bounds__(kMedLongWG) void k_window_median_long(const int64_t
 
 struct MedianVariant {
     const void* fn;
-    int cols;  // columns per tile
+    int cols;   // columns per tile
+    int64_t most;  // columns C whose rows of one wave lie within 32-bit offsets
 };
 
 template <int PARTS, int W>
 MedianVariant median_variant()
 {
-    return MedianVariant{reinterpret_cast<const void*>(&k_window_median<PARTS, W>), kMedWG / PARTS};
+    // a wave's load takes PARTS / 4 rows, or a part of one
+    return MedianVariant{reinterpret_cast<const void*>(&k_window_median<PARTS, W>), kMedWG / PARTS,
+                         PARTS <= 4 ? INT64_MAX : (int64_t)(UINT32_MAX / 8 / (PARTS / 4)) - 1};
 }
 
 // By the longest window's steps.  Past 512 steps W = 2: twice the columns per
@@ -497,7 +500,8 @@ SF_API int sf_window_median(const int64_t* durations, int64_t T, int32_t R, int3
     if (device_cus(stream, &cus) != SF_OK) return SF_EHIP;
     if (cus < 1) cus = 1;
     const int64_t C = (int64_t)S * R;
-    if (n_max > kMedTileRows || C < 2 || C > (int64_t)(UINT32_MAX / 8 / 16)) {
+    const MedianVariant v = pick_median(n_max);
+    if (n_max > kMedTileRows || C < 2 || C > v.most) {
         const int64_t total = W * C;
         const int64_t want = (total + kMedLongWG / 64 - 1) / (kMedLongWG / 64);
         const int64_t grid = want < (int64_t)cus * 8 ? want : (int64_t)cus * 8;
@@ -508,7 +512,6 @@ SF_API int sf_window_median(const int64_t* durations, int64_t T, int32_t R, int3
         return launch(reinterpret_cast<const void*>(&k_window_median_long), dim3((unsigned)grid),
                       dim3(kMedLongWG), args, 0, stream);
     }
-    const MedianVariant v = pick_median(n_max);
     int64_t nchunk = (C + v.cols - 1) / v.cols;
     int64_t tiles = W * nchunk;
     const int64_t most = (int64_t)cus * (n_max <= 512 ? 2 : 1);

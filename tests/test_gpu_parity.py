@@ -1549,3 +1549,16 @@ def test_median_many_tiles(sf, S, R, T, window):
     d[:window, 0, R - 1] = (3 << 33) + rng.integers(0, 3, size=window)
     print("case S=%d R=%d T=%d window=%d" % (S, R, T, window), flush=True)
     assert_median_equal(sf, d, window)
+
+
+@pytest.mark.parametrize("S,R", [(513, 65535), (514, 65536)])
+def test_median_many_columns(sf, S, R):
+    """More than 2^25 (stage, rank) columns, whose rows lie more than 2^32 / 16
+    bytes apart: windows of two steps and a last one of a single step, against
+    the smaller of the two and the step itself."""
+    gen = torch.Generator(device=DEV).manual_seed(S)
+    d = torch.randint(0, 1 << 33, (3, S, R), dtype=torch.int64, device=DEV, generator=gen)
+    print("case S=%d R=%d" % (S, R), flush=True)
+    med = sf.sf_window_median(d, 2)
+    assert torch.equal(med[0], torch.minimum(d[0], d[1]))
+    assert torch.equal(med[1], d[2])

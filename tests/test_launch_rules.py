@@ -147,3 +147,13 @@ def test_gain_of_few_steps(recorder, R, S, T, near):
                                        (2048, 513, "256, 4, 1")])
 def test_gain_wide_workgroups_for_few_steps(recorder, R, T, shape):
     assert ", ".join(template_args(kernels(recorder, "sf_exposure_gain", R, 12, T, 50)[0])) == shape
+
+
+@pytest.mark.parametrize("R,S,T,window,tiled", [
+    (65536, 512, 3, 2, True), (65536, 520, 3, 2, True), (65536, 9000, 2, 2, True), (65536, 520, 300, 300, True),
+    (4096, 12, 4096, 4096, True), (4096, 12, 4097, 4097, False), (1, 1, 50, 10, False)])
+def test_median_tiles(recorder, R, S, T, window, tiled):
+    """Windows of up to 4096 steps are held in tiles, at any stage and rank
+    count."""
+    name = kernels(recorder, "sf_window_median", R, S, T, window)[0]
+    assert name.startswith("k_window_median<") == tiled, name
