@@ -90,6 +90,13 @@ def row_cpu(samples: int, secs: float, what: str) -> dict:
             "sample": "%s (%d samples, %.2f s)" % (what, samples, secs)}
 
 
+def gain_kernel(R: int, S: int) -> str:
+    """The kernel that sf_exposure_gain takes for a workload's thousands of steps."""
+    if 128 < R <= 32768 and (S >= 13 or (S >= 9 and R <= 16384) or (S >= 7 and R <= 2048)):
+        return "k_exposure_gain_near"
+    return "k_exposure_gain_wide" if R <= 8 else "k_exposure_gain"
+
+
 def main() -> int:
     ap = argparse.ArgumentParser(description=__doc__)
     ap.add_argument("--gpus", type=int, default=1)
@@ -573,9 +580,7 @@ def main() -> int:
             wg = g_out["window_gain"].sum(dim=0).double()
             wm = float(g_out["window_makespan"].sum())
             next_rows["exposure_gain"] = {
-                "kernel": ("k_exposure_gain_near (+ k_window_sum)"
-                           if S >= 9 and 128 < R <= 32768
-                           else "k_exposure_gain (+ k_window_sum)"),
+                "kernel": gain_kernel(R, S) + " (+ k_window_sum)",
                 "bound": "hbm",
                 "launch_ms": g_ms,
                 "algorithmic_bytes_per_launch": g_bytes,

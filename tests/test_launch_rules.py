@@ -157,3 +157,11 @@ def test_median_tiles(recorder, R, S, T, window, tiled):
     count."""
     name = kernels(recorder, "sf_window_median", R, S, T, window)[0]
     assert name.startswith("k_window_median<") == tiled, name
+
+
+def test_bench_names_the_gain_kernel_that_runs(recorder):
+    import bench
+    import synth
+    for wl in synth.WORKLOADS.values():
+        name = kernels(recorder, "sf_exposure_gain", wl.R, wl.S, wl.T, wl.window)[0]
+        assert name.startswith(bench.gain_kernel(wl.R, wl.S) + "<"), (wl.name, name)
