@@ -1,7 +1,7 @@
 """GPU path against the CPU oracle, element by element (bit-exact: every
 output is integer ns or an index).  Shapes sweep every launch variant of the
-frontier kernel (tile widths, 8- and 16-byte loads, several tiles per rank
-row, ragged rank and step counts), the window kernels (ragged last window,
+frontier kernel (tile widths, rank pairs at 8- and 16-byte alignment, several
+tiles per rank row, ragged rank and step counts), the window kernels (ragged last window,
 several rank chunks, leaders outside [0, R)), and the degenerate cases."""
 import numpy as np
 import pytest
@@ -57,7 +57,7 @@ def assert_summary_equal(sf, inc, lead, R, window):
 
 
 # rank counts at and around every tile boundary of the launch table, odd
-# counts (8-byte loads), several tiles per row (R > 4096) and the maximum
+# counts (an overlapping last pair), several tiles per row and the maximum
 RANKS = [1, 2, 3, 7, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257,
          511, 512, 513, 1000, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097,
          8192, 12289, 16384]
@@ -267,7 +267,7 @@ def test_frontier_golden_examples(sf):
 
 
 def test_frontier_misaligned_base_uses_narrow_loads(sf):
-    """A base that is 8- but not 16-byte aligned takes the 8-byte-load path."""
+    """A base that is 8- but not 16-byte aligned takes the same 16-byte loads."""
     T, S, R = 20, 6, 256
     d = synth.random_durations(T, S, R, seed=5, hi=1000)
     flat = torch.zeros(T * S * R + 1, dtype=torch.int64, device=DEV)
@@ -669,7 +669,7 @@ def test_evidence_stage_sweep(sf, S):
 def test_evidence_large_stage_counts(sf, S, R):
     """Stage counts past what LDS holds (the accumulation expansion of
     Sec. 3): from 820 stages the partial results of a step go through its
-    own output rows.  Odd rank counts (8-byte loads), rank tiles with a
+    own output rows.  Odd rank counts (an overlapping last pair), rank tiles with a
     ragged last one, step counts ragged against the steps a workgroup holds,
     tie-heavy and wide values."""
     T = max(2, min(37, (1 << 25) // (R * S)))
@@ -820,9 +820,9 @@ def test_gain_stage_sweep(sf, S):
 
 
 def test_gain_many_stages_wide_values(sf):
-    """Past 64 stages (the two-pass kernel): several rank tiles with a
-    ragged last one, odd ranks (8-byte loads), wide values, a window
-    boundary inside a workgroup's steps."""
+    """Past the stages that registers hold: several ranks per lane with a
+    ragged end, odd ranks, wide values, a window boundary between a
+    workgroup's steps."""
     rng = np.random.Generator(np.random.PCG64(128))
     for T, S, R, window, hi in ((9, 128, 16384, 4, 10**9), (13, 100, 301, 5, 1 << 40),
                                 (6, 65, 129, 2, 3)):
@@ -879,9 +879,9 @@ def test_gain_stalled_near_frontier(sf):
 
 
 def test_gain_wide_steps_among_narrow(sf):
-    """Past 4096 ranks: the odd steps hold a duration past 2^32 (their
-    totals span more than 2^32: the bound's radix passes run in 64 bits),
-    the even ones stay below (32-bit passes), in one launch."""
+    """Past 4096 ranks: the odd steps hold a duration past 2^32, so that
+    their totals span more than that, the even ones stay below, in one
+    launch."""
     rng = np.random.Generator(np.random.PCG64(717))
     T, S, R, window = 9, 12, 8192, 4
     d = rng.integers(0, 1 << 28, size=(T, S, R), dtype=np.int64)
@@ -1034,9 +1034,10 @@ def test_lag_rank_sweep(sf, R):
 
 @pytest.mark.parametrize("R", [1024, 2048, 4096, 8192, 16384])
 def test_narrow_pass_hand_over(sf, R):
-    """At 1024 to 16384 ranks the raw spread, and at 8192 and 16384 the lag,
-    run on 32-bit values and hand a step whose values leave 32 bits to the
-    64-bit kernel:
+    """At 1024 to 16384 ranks the raw spread runs on 32-bit values and hands a
+    row whose values leave 32 bits to the 64-bit kernel; the lag of so few
+    steps shares their stages among workgroups, in 64 bits (its own hand-over:
+    test_lag_hand_over):
     a duration of 2^32 or more, a rebased prefix that carries past 2^32 at
     a later stage, an overflow at the last stage only, neighbours that stay
     narrow, and every step handed over; all against the oracle."""
@@ -1111,8 +1112,8 @@ def test_spread_hand_over(sf, R, S, T):
 def test_lag_spread_past_16384_ranks(sf, R):
     """More ranks than a step holds in 64-bit registers: up to 32768 the
     32-bit pass with 32 values per lane (partial last tile for R below it)
-    and the streaming 64-bit kernel for the steps it hands over; odd R and
-    more than 32768 ranks the streaming kernel alone.  Tie-heavy and wide
+    and the streaming 64-bit kernel for the steps it hands over; more than
+    32768 ranks the streaming kernel alone.  Tie-heavy and wide
     values, and steps forced past 32 bits (a duration of 2^32 + 5, a prefix
     spread past 2^32 at a later stage) next to steps that stay narrow."""
     rng = np.random.Generator(np.random.PCG64(R))
@@ -1137,9 +1138,9 @@ def test_lag_spread_past_16384_ranks(sf, R):
 
 @pytest.mark.parametrize("R", [4096, 16384])
 def test_lag_spread_misaligned_large(sf, R):
-    """A base 8 bytes past 16-byte alignment takes the 8-byte-load shapes
-    (64-bit, full tiles) at the rank counts whose aligned calls take the
-    32-bit pass; wide and narrow values alike."""
+    """A base 8 bytes past 16-byte alignment, at rank counts that fill a tile:
+    the raw spread's 32-bit pass and hand-over, the lag shared by stages; wide
+    and narrow values alike."""
     rng = np.random.Generator(np.random.PCG64(R + 29))
     T, S = 6, 3
     d = rng.integers(0, 10**7, size=(T, S, R), dtype=np.int64)
@@ -1226,7 +1227,7 @@ def test_spread_pins_and_layouts(sf):
     for S in (1, 12, 512):
         d = synth.random_durations(3, S, 33, seed=S, hi=10**6)
         assert_spread_equal(sf, d, 2)
-    T, S, R = 7, 5, 402                          # 8-byte aligned base: 8-byte loads
+    T, S, R = 7, 5, 402                          # 8-byte aligned base
     d = synth.random_durations(T, S, R, seed=4, hi=10**5)
     flat = torch.zeros(T * S * R + 1, dtype=torch.int64, device=DEV)
     flat[1:] = torch.from_numpy(d.reshape(-1)).to(DEV)
@@ -1268,9 +1269,8 @@ def test_median_window_sweep(sf, window):
 @pytest.mark.parametrize("R", [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256,
                                257, 1000, 4097])
 def test_median_rank_sweep(sf, R):
-    """Rank counts at the edges of every tile width (32 ranks for windows
-    of up to 1024 steps, 64 up to 512, 128 up to 256, 256 up to 128), odd
-    counts (8-byte loads) and a partial last tile."""
+    """Rank counts around the tile widths (256 columns of a window of up to 64
+    steps to 8 of one of 4096), odd counts and a partial last tile."""
     for window, T in ((100, 250), (200, 410), (400, 800), (1000, 1100)):
         d = synth.random_durations(T, 2, R, seed=R + window, hi=10**7)
         print("case R=%d window=%d T=%d" % (R, window, T), flush=True)
@@ -1279,15 +1279,11 @@ def test_median_rank_sweep(sf, R):
 
 @pytest.mark.parametrize("window", [100, 250, 1000])
 def test_median_warm_start_edges(sf, window):
-    """The warm start of the window median (a column's median bracketed
-    around the same rank's median of the window before, or in a unit's
-    first window around a median already found in the tile) must give the
-    oracle's median whether the guess lands inside its bracket, just past
-    its edge or far off, and when the bracket holds too many values: window
-    scales that drift by 0 to 60% from one window to the next, ranks whose
-    scales differ 50-fold inside one tile, constant columns and columns of
-    mass ties (every value in the bracket), values next to 2^32 (no bracket
-    fits below 2^32), zeros, and a ragged last window."""
+    """Windows whose medians lie close to, or far from, those of the window
+    before and of the columns beside them: window scales that drift by 0 to
+    60% from one window to the next, ranks whose scales differ 50-fold inside
+    one tile, constant columns and columns of mass ties, values next to 2^32,
+    zeros, and a ragged last window."""
     rng = np.random.Generator(np.random.PCG64(window))
     R, S = 96, 3
     shifts = [0.0, 0.004, -0.008, 0.012, 0.02, -0.03, 0.05, 0.5, -0.6, 1e-4]
