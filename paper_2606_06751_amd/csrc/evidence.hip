@@ -356,7 +356,8 @@ size_t ev_lds_need(const EvidenceVariant& v, int R, int S, bool gtab)
 // ranks, one wave per step, up to 1024 steps (100 x 12: 600 steps 13.8 -> 10.8,
 // 1200 14.7 -> 16.1).  Past 8192 ranks all 1024 lanes, one workgroup per CU, up
 // to 256 steps (16384 x 8: 150 steps 46 -> 40, 300 74 -> 86) and where the last
-// tile is half full at least (24576 x 8 x 50 66 -> 74, 32768 88 -> 81).  From 1025
+// tile is half full at least (24576 x 8 x 50 66 -> 74, 32768 88 -> 81; at 128
+// VGPRs they spill 4, at odd ranks 7).  From 1025
 // to 8192 ranks the reductions of so many waves cost more than they hide.
 static bool ev_deep(int64_t T, int R, int S)
 {

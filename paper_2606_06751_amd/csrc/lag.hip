@@ -121,7 +121,8 @@ constexpr int64_t kRedo = INT64_MIN;  // outputs are >= 0 under the data contrac
 // before its own (without selects), and resolves the boundary before its
 // first once more for the increment.  A boundary costs 2 to 3 us in series
 // (LDS latency and barriers), its durations a re-read from the caches: 429
-// ranks x 220 stages x 128 steps 616 -> 222 us.
+// ranks x 220 stages x 128 steps 616 -> 222 us.  At odd ranks past 512 its loads
+// of 8 bytes each spill 6 to 9 VGPRs.
 
 // Steps per workgroup (SC) of the REDO launch.  One workgroup for each of 10000
 // steps costs 14 us where none is marked (about 1 ns per workgroup and up), but
@@ -305,7 +306,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(NARROW ? (K 
             // stages: at 16 values per lane it takes four loads at a time
             // (with the select's tests in 32 bits this fits the 64-VGPR
             // budget; measured at 16384 ranks 3% faster than two at a time,
-            // which the 64-bit tests forced); at 32 values, two at a time
+            // which the 64-bit tests forced); at 32 values, two at a time (the
+            // 12-wave lag, at 80 VGPRs, spills 8 at even and 10 at odd ranks; four
+            // at a time spilled 20 and 24: 24576 ranks x 12 x 1000 550 -> 460 us)
             constexpr int CH = WG == 768 ? (PREFIX ? NLD / 2 : NLD / 4) : PREFIX ? (K == 16 ? 2 : NLD / 2) : 2;
             // the stage row through a buffer resource: its base in SGPRs, a
             // lane's offset in one VGPR (FULL: the same for every load); of
@@ -745,7 +748,9 @@ LagVariant lag_wide(int64_t T, int R)
     const void* redo = reinterpret_cast<const void*>(&k_median_stream<PREFIX, true>);
     if (R <= 32 * 768 && T > 256) return LagVariant{lag_kernel<PREFIX, VEC, 32, 768, false, true>(), 768, redo, kStreamWG};
     if (R < 32 * 1024) return LagVariant{lag_kernel<PREFIX, VEC, 32, 1024, false, true>(), 1024, redo, kStreamWG};
-    if (R == 32 * 1024) return LagVariant{lag_kernel<PREFIX, VEC, 32, 1024, true, true>(), 1024, redo, kStreamWG};
+    if constexpr (VEC == 2) {
+        if (R == 32 * 1024) return LagVariant{lag_kernel<PREFIX, VEC, 32, 1024, true, true>(), 1024, redo, kStreamWG};
+    }
     return LagVariant{reinterpret_cast<const void*>(&k_median_stream<PREFIX, false>), kStreamWG, nullptr, 0};
 }
 
@@ -758,10 +763,12 @@ LagVariant lag_shape(int R, bool split)
     }
     if constexpr (K == 16 && (WG >= 512 || !PREFIX)) {
         const void* redo = lag_kernel<PREFIX, VEC, K, WG, false, false, true>();
-        if (R == K * WG) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true, true>(), WG, redo, WG};
+        if constexpr (VEC == 2) {  // (an odd R fills no tile)
+            if (R == K * WG) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true, true>(), WG, redo, WG};
+        }
         return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false, true>(), WG, redo, WG};
     } else {
-        if constexpr (!pubu) {
+        if constexpr (!pubu && VEC == 2) {
             if (R == K * WG) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, true>(), WG, nullptr, 0};
         }
         return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false>(), WG, nullptr, 0};

@@ -71,13 +71,6 @@ __device__ __forceinline__ u64 wave_or64(u64 v)
     return ((u64)wave_or32((uint32_t)(v >> 32)) << 32) | wave_or32((uint32_t)v);
 }
 
-// the position of this lane among the lanes of `mask` below it
-__device__ __forceinline__ uint32_t lane_rank(u64 mask)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 template <typename V>
 __device__ __forceinline__ bool sel_match_t(V u, int hi, V prefix)
 {
