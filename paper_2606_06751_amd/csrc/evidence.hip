@@ -385,8 +385,9 @@ EvidenceVariant pick_evidence_deep(int R)
 // x 8192: 356 -> 164 us, 671 x 8 x 8192 85 -> 63, 1024 x 12 x 8192 149 -> 128,
 // 6001 x 10 x 1024 133 -> 84; 250 ranks on 32 lanes level, 256 110 against
 // 115, 240 x 12 x 16000 72 against 67; 8192 ranks at 16 each, 32 MB of rows and more, 126 against 130).  A
-// shape whose LDS would exceed 64 KB at this S falls back to two 64-lane slots per step
-// (80 * S bytes, at most 40 KB).
+// shape whose LDS would exceed 64 KB at this S falls back to half as many lanes
+// (512 lanes past 204 stages: 8192 x 260, one step 1523 -> 600 us), else to two
+// 64-lane slots per step (80 * S bytes, at most 64 KB).
 template <int V>
 EvidenceVariant pick_evidence(int64_t T, int R, int S)
 {
@@ -415,6 +416,7 @@ EvidenceVariant pick_evidence(int64_t T, int R, int S)
     else if (R <= 8192 && T < 400) v = ev_variant<V, 16, 512, 512>(0);
     else if (R > 8192 && R <= 12288) v = ev_variant<V, 24, 512, 512>(0);
     else v = ev_variant<V, 32, 256, 256>(0);
+    if (v.WG == 512 && ev_lds_need(v, R, S, false) > kLdsMaxPerWg) v = ev_variant<V, 32, 256, 256>(0);
     if (ev_lds_need(v, R, S, false) > kLdsMaxPerWg) v = ev_variant<V, 16, 128, 128>(0);
     return v;
 }

@@ -680,6 +680,13 @@ def test_evidence_large_stage_counts(sf, S, R):
         assert_evidence_equal(sf, d)
 
 
+@pytest.mark.parametrize("R,S", [(8192, 204), (8192, 205), (5001, 260), (12000, 260), (8192, 410)])
+def test_evidence_narrower_groups(sf, R, S):
+    """Stage counts whose table past 4096 ranks fits fewer lanes per step only."""
+    for hi in (3, (1 << 47) // S - 1):
+        assert_evidence_equal(sf, synth.random_durations(2, S, R, seed=S + R, hi=hi))
+
+
 def test_evidence_max_ranks_and_odd_base(sf):
     d = synth.random_durations(2, 3, sf.SF_MAX_R, seed=19, hi=1)
     assert_evidence_equal(sf, d)

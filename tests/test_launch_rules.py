@@ -90,7 +90,9 @@ def test_frontier_rows_in_flight(recorder, R, S, T, rows):
     (4, 5, 100000, "2, 4, 64, false, 1"), (4, 8, 100000, "2, 4, 64, false, 4"), (16, 7, 100000, "2, 8, 64, false, 1"),
     (100, 12, 1024, "2, 64, 64, false, 4"), (100, 12, 1200, "8, 16, 256, false, 1"), (200, 6, 1536, "2, 128, 128, false, 4"),
     (129, 6, 2000, "8, 32, 64, false, 1"), (240, 12, 16000, "8, 16, 256, false, 1"), (16384, 8, 256, "16, 1024, 1024, false, 1"),
-    (16384, 8, 300, "32, 256, 256, false, 1"), (24576, 8, 50, "32, 256, 256, false, 1"), (32768, 8, 50, "16, 1024, 1024, false, 1")])
+    (16384, 8, 300, "32, 256, 256, false, 1"), (24576, 8, 50, "32, 256, 256, false, 1"), (32768, 8, 50, "16, 1024, 1024, false, 1"),
+    (8192, 204, 1, "16, 512, 512, false, 1"), (8192, 205, 1, "32, 256, 256, false, 1"), (5001, 260, 20, "32, 256, 256, false, 1"),
+    (12000, 260, 500, "32, 256, 256, false, 1"), (8192, 410, 1, "16, 128, 128, false, 1")])
 def test_evidence_shapes(recorder, R, S, T, shape):
     """The shapes for few steps and few ranks end where they were measured to
     be the faster ones."""
