@@ -353,10 +353,10 @@ int sf_window_summary(const int64_t* increment, const int32_t* leader,
  * same steps, as one call: the per-step accounting of Sec. 3 (Eq. (1)) and
  * its reduction over windows (Eq. (2) numerators, lead counts, the top-2 of
  * Sec. 4).  Small inputs (R <= 256, S <= 12, T * S * R <= 2^20 samples, and
- * windows of 256 steps at 8 ranks to about 10 at 256) run as ONE kernel
- * launch, one workgroup per window, for callers bound by launch latency (a
- * per-step or per-window serving loop); larger ones run the two calls'
- * kernels, of which the second is one launch too.  Every output is
+ * windows of 256 steps at 8 ranks (1024 of one stage) to about 10 at 256)
+ * run as ONE kernel launch, one workgroup per window, for callers bound by
+ * launch latency (a per-step or per-window serving loop); larger ones run the
+ * two calls' kernels, of which the second is one launch too.  Every output is
  * identical to sf_frontier's and sf_window_summary's.
  *
  *   durations          [T][S][R] int64 ns (as for sf_frontier).

@@ -298,13 +298,16 @@ static int launch_whole(const int64_t* inc, const int32_t* lead, int64_t T, int 
 // the group's last lane writes each boundary's advance and leader as soon as
 // the stage is reduced and adds them into the window's LDS totals and lead
 // counts; then the workgroup writes the counts and picks the top-2.  One launch
-// instead of two (8 ranks x 6 x 1000, windows of 100: 6.1 against 7.1 us).  It
+// instead of two (8 ranks x 6 x 1000, windows of 100: 6.3 against 7.7 us).  It
 // takes windows whose steps x stages are about one round of steps, since
 // further rounds, and chunks of rows, cost a memory latency each in series while
 // the other CUs idle; measured against the two launches, in us: 16 ranks x 6,
-// windows of 50 6.0 : 7.6, of 200 9.5 : 7.2; 32 x 6, of 20 5.8 : 7.2, of 100 9.2 :
-// 7.3; 64 x 4, of 20 6.6 : 7.7, of 50 9.1 : 7.6; 256 x 4, of 10 7.2 : 8.5, of 50
-// 12.5 : 8.9; 8 x 12, of 50 7.4 : 7.6, of 200 9.7 : 8.5.
+// windows of 50 6.7 : 7.5, of 200 10.0 : 7.8; 32 x 6, of 20 6.7 : 7.7, of 100 10.4 :
+// 8.0; 64 x 4, of 20 6.6 : 7.5, of 50 8.6 : 7.6; 256 x 4, of 10 6.9 : 8.3, of 50
+// 11.1 : 8.7; 8 x 12, of 50 8.4 : 8.5, of 200 10.7 : 9.2.  Up to 16 ranks two to four
+// rounds of few stages are still the faster way (8 ranks, in windows of 512: one
+// stage 5.5 : 7.8, two 6.6 : 8.1, four 8.6 : 7.8; one stage in windows of 1024 7.4 :
+// 7.9; 16 ranks x 1, of 300 5.7 : 7.6, of 600 7.9 : 7.8).
 constexpr int kFusedMaxR = 256;
 constexpr int kFusedMaxS = 12;
 constexpr int64_t kFusedMaxWindow = 256;
@@ -313,7 +316,9 @@ constexpr int64_t kFusedMaxSamples = 1 << 20;
 static bool fused_fits(int64_t T, int R, int S, int64_t window)
 {
     const int64_t n = window < T ? window : T;
-    if (R > kFusedMaxR || S > kFusedMaxS || n > kFusedMaxWindow || T * S * (int64_t)R > kFusedMaxSamples) return false;
+    if (R > kFusedMaxR || S > kFusedMaxS || T * S * (int64_t)R > kFusedMaxSamples) return false;
+    if (n > kFusedMaxWindow)
+        return R <= 8 ? n <= 4 * kFusedMaxWindow && n * S <= 1280 : R <= 16 && n <= 400 && n * S <= 640;
     return n * S <= (R <= 8 ? 2048 : R <= 16 ? 640 : R <= 32 ? 300 : R <= 64 ? 120 : 80);
 }
 

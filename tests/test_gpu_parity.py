@@ -397,6 +397,10 @@ def test_frontier_summary_fused(sf, R):
     cases = [(37, 5, 10, 3), (250, 6, 100, 10**6), (33, 64, 7, 2), (20, 65, 6, 5)]
     if R <= 32:
         cases += [(1030, 2, 1030, 10**4), (2100, 2, 1025, 4)]
+    if R <= 9:
+        cases += [(3000, 1, 1024, 9), (1200, 2, 512, 10**6), (700, 3, 426, 4)]
+    if R <= 17:
+        cases += [(1000, 1, 400, 10**6), (700, 2, 320, 3)]
     cases.append(((1 << 20) // (4 * R) + 3, 4, 64, 10**5))  # just past 2^20 samples
     for T, S, window, hi in cases:
         d = synth.random_durations(T, S, R, seed=R * 7 + S + window, hi=hi)

@@ -116,6 +116,8 @@ def test_whole_windows(recorder, call, R, S, T, window, whole):
 
 @pytest.mark.parametrize("R,S,window,fused", [
     (8, 6, 100, True), (8, 12, 100, True), (8, 12, 200, False), (16, 6, 100, True), (16, 6, 200, False), (32, 6, 50, True),
+    (8, 6, 256, True), (8, 1, 1024, True), (8, 1, 1025, False), (4, 2, 640, True), (2, 3, 427, False), (16, 1, 400, True),
+    (16, 1, 401, False), (16, 2, 321, False), (17, 1, 257, False),
     (32, 6, 100, False), (64, 4, 20, True), (64, 8, 1, True), (64, 6, 50, False), (256, 4, 20, True), (256, 6, 50, False),
     (200, 8, 1, True), (257, 1, 1, False), (8, 13, 10, False)])
 def test_fused_summary(recorder, R, S, window, fused):
