@@ -132,8 +132,10 @@ constexpr int64_t kRedo = INT64_MIN;  // outputs are >= 0 under the data contrac
 // 128 VGPRs; the streaming kernel takes half of that), four times as many
 // where that is below kRedoGroups, and a workgroup looks at up to kRedoRows steps.
 // They lie a whole grid apart, so a stretch of marked steps is shared out, and
-// where the steps are the rows of several stages, the grid has no factor in
-// common with the stages: one long stage is not one workgroup's every time.
+// the grid has no factor in common with the stages whose rows are steps, nor
+// with 2, 3, 5 and 7: neither one long stage nor every tenth step is one
+// workgroup's every time (16384 ranks x 12 x 2000, every tenth step marked:
+// 674 -> 590 us).
 constexpr int kRedoRows = 8;
 constexpr int64_t kRedoWaves = 4096;   // resident on the chip
 constexpr int64_t kRedoGroups = 4096;  // at least the workgroups of one wave that are
@@ -152,7 +154,7 @@ static RedoGrid redo_grid(int64_t T, int waves, bool streaming, int stages)
     RedoGrid g;
     g.rows = (int)((T + most * rounds - 1) / (most * rounds));
     g.blocks = (T + g.rows - 1) / g.rows;
-    while (g.rows > 1 && std::gcd(g.blocks, (int64_t)stages) != 1) ++g.blocks;
+    while (g.rows > 1 && std::gcd(g.blocks, (int64_t)210 * stages) != 1) ++g.blocks;
     return g;
 }
 

@@ -169,3 +169,13 @@ def test_bench_names_the_gain_kernel_that_runs(recorder):
     for wl in synth.WORKLOADS.values():
         name = kernels(recorder, "sf_exposure_gain", wl.R, wl.S, wl.T, wl.window)[0]
         assert name.startswith(bench.gain_kernel(wl.R, wl.S) + "<"), (wl.name, name)
+
+
+def test_hand_over_grid_meets_no_short_period(recorder):
+    """Every second to tenth step marked is not one workgroup's every time."""
+    import math
+    cases = [("sf_frontier_lag", R, S, T, 1) for R, S, T in ((16384, 12, 2000), (8192, 3, 5000), (5001, 8, 10000), (20000, 8, 6000))]
+    cases.append(("sf_rank_spread", 1024, 9, 20000, 100))
+    for c, ls in zip(cases, launches(recorder, cases)):
+        steps, redo = ls[0].grid, ls[1]
+        assert redo.grid < steps and math.gcd(redo.grid, 210) == 1, (c, ls)
