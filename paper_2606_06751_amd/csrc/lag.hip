@@ -21,6 +21,7 @@
 #include "sf_host.h"
 #include "sf_select.h"
 
+#include <algorithm>
 #include <numeric>
 #include <type_traits>
 
@@ -757,11 +758,14 @@ LagVariant lag_wide(int64_t T, int R)
 }
 
 template <bool PREFIX, int VEC, int K, int WG>
-LagVariant lag_shape(int R, bool split)
+LagVariant lag_shape(int R, bool split, bool in_one = false)
 {
     constexpr bool pubu = PREFIX && K == 16 && WG <= 256;
     if constexpr (PREFIX) {
         if (split) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false, false, false, true>(), WG, nullptr, 0};
+    }
+    if constexpr (K == 16 && WG >= 512 && PREFIX) {
+        if (in_one) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false>(), WG, nullptr, 0};
     }
     if constexpr (K == 16 && (WG >= 512 || !PREFIX)) {
         const void* redo = lag_kernel<PREFIX, VEC, K, WG, false, false, true>();
@@ -781,7 +785,7 @@ LagVariant lag_shape(int R, bool split)
 // the registers allow: a wave spends less time at barriers than a lane does
 // on 4x the prefixes (measured on the 128- to 16384-rank workloads).
 template <bool PREFIX, int VEC>
-LagVariant pick_lag(int64_t T, int R, bool split)
+LagVariant pick_lag(int64_t T, int R, bool split, bool in_one)
 {
     if (R <= 128) return lag_shape<PREFIX, VEC, 2, 64>(R, split);
     if (R <= 256) return lag_shape<PREFIX, VEC, 4, 64>(R, split);
@@ -789,14 +793,49 @@ LagVariant pick_lag(int64_t T, int R, bool split)
     if (R <= 1024) return lag_shape<PREFIX, VEC, 16, 64>(R, split);
     if (R <= 2048) return lag_shape<PREFIX, VEC, 16, 128>(R, split);
     if (R <= 4096) return lag_shape<PREFIX, VEC, 16, 256>(R, split);
-    if (R <= 8192) return lag_shape<PREFIX, VEC, 16, 512>(R, split);
-    if (R <= 16384) return lag_shape<PREFIX, VEC, 16, 1024>(R, split);
+    if (R <= 8192) return lag_shape<PREFIX, VEC, 16, 512>(R, split, in_one);
+    if (R <= 16384) return lag_shape<PREFIX, VEC, 16, 1024>(R, split, in_one);
     return lag_wide<PREFIX, VEC>(T, R);  // R <= SF_MAX_R
 }
 
-// Waves that a split lag aims at, and below which the raw spread takes rows
-// for steps.
+// Workgroups that share a step's stages in the lag of few steps, where that
+// fills the chip (128 steps: 1024 ranks x 8 32 -> 13 us, 16384 x 12 97 -> 73).
+// Up to 4096 ranks about kLagWaves waves, at least four workgroups (1024 steps of
+// 1264 ranks, two each: 42 -> 48 us), at odd ranks past 512, loaded 8 bytes at a
+// time, at least six (1023 x 8, four of them 38 -> 40, eight 36 -> 31).  Past
+// that, what runs in one round, since a second one costs more than the split
+// saves (10000 x 8 x 160, two each: 52 -> 74): one workgroup per CU past 8192
+// ranks, up to there two where a step has more than four stages (4140 x 8: 160
+// steps, three each, 36 -> 28, 256, two each, 36 -> 34; 8190, 45 -> 47; 6001, loaded
+// 8 bytes at a time, 46 -> 53), and no more than four per step where that is more
+// than one per CU (48 steps of 6001 x 8: four 25, eight 30).  Two stages gain
+// nothing: the second workgroup resolves the first boundary too.
 constexpr int64_t kLagWaves = 4096;
+constexpr int64_t kLagCUs = 256;
+
+static int64_t lag_units(int64_t T, int R, int S)
+{
+    if (R > 16384) return 1;
+    if (R <= 4096) {
+        const int64_t units = std::min<int64_t>(kLagWaves / (T * (R <= 1024 ? 1 : (R + 1023) / 1024)), S);
+        return units < (R > 512 && (R & 1) ? 6 : 4) ? 1 : units;
+    }
+    int64_t units = kLagCUs / T;
+    if (R <= 8192 && S > 4) units = std::min<int64_t>(2 * kLagCUs / T, std::max<int64_t>(4, units));
+    if (S <= 2 || (T > kLagCUs / 2 && units < 3 && ((R & 1) || R > 6144))) return 1;
+    return std::max<int64_t>(1, std::min<int64_t>(units, S));
+}
+
+// A step's stages by one workgroup, in 64 bits, in one round: past 4096 ranks
+// the 32-bit pass gains nothing there, and the launch behind it costs 2 us
+// (10000 ranks x 2 x 220 18.5 -> 15.5 us, 4140 x 1 x 100 8.6 -> 6.5, 12001 x 8 x 256
+// 71 -> 67).
+static bool lag_in_one(int64_t T, int R)
+{
+    return R > 4096 && R <= 16384 && T <= (R <= 8192 ? 2 : 1) * kLagCUs;
+}
+
+// Waves below which the raw spread takes rows for steps.
 constexpr int64_t kSpreadWaves = 8192;
 
 // The narrow pass, then (if it has one) the 64-bit pass over the steps it
@@ -806,11 +845,8 @@ constexpr int64_t kSpreadWaves = 8192;
 // become steps of one stage each (measured: 16 steps 5 to 60 times faster,
 // 1024 steps of 1024 ranks 39 -> 21 us; past 4096 ranks always, 8192 x 12 x
 // 1024 141 -> 126; at 8192 waves and up to 512 ranks still 72 -> 65, at 1024
-// ranks 99 -> 103).  The lag shares a step's stages among workgroups, where
-// that makes at least four of them, or two past 4096 ranks (128 steps: 1024
-// ranks x 8 32 -> 13 us, 16384 x 12 97 -> 73; 1024 steps of 1264 ranks,
-// two each: 42 -> 48; odd ranks past 512, loaded 8 bytes at a time, at least
-// six: 1023 x 8, four of them 38 -> 40, eight 36 -> 31).
+// ranks 99 -> 103).  The lag shares a step's stages among workgroups
+// (lag_units).
 template <bool PREFIX>
 static int launch_lag(const int64_t* d, int64_t T, int R, int S, int64_t* out, int64_t* out_inc,
                       sf_stream_t stream)
@@ -819,20 +855,19 @@ static int launch_lag(const int64_t* d, int64_t T, int R, int S, int64_t* out, i
     const int stages = S;
     int64_t units = 1;
     int SC = S;
+    bool in_one = false;
     if (PREFIX) {
-        units = kLagWaves / waves;
-        if (units > S) units = S;
-        if (R > 16384 || units < (R > 4096 ? 2 : R > 512 && (R & 1) ? 6 : 4)) units = 1;
+        units = lag_units(T, R, S);
         SC = (int)((S + units - 1) / units);
         units = (S + SC - 1) / SC;
+        in_one = units == 1 && lag_in_one(T, R);
     } else if ((waves < kSpreadWaves || R > 4096 || (R <= 512 && waves <= kSpreadWaves * 3 / 2)) &&
                T <= INT32_MAX / S) {
         T *= S;
         S = SC = 1;
     }
-    const bool split = units > 1;
     const bool vec2 = (R & 1) == 0;
-    const LagVariant v = vec2 ? pick_lag<PREFIX, 2>(T, R, split) : pick_lag<PREFIX, 1>(T, R, split);
+    const LagVariant v = vec2 ? pick_lag<PREFIX, 2>(T, R, units > 1, in_one) : pick_lag<PREFIX, 1>(T, R, units > 1, in_one);
     void* args[] = {(void*)&d, (void*)&T, (void*)&R, (void*)&S, (void*)&out, (void*)&out_inc, (void*)&SC};
     int rc = launch(v.fn, dim3((unsigned)(T * units)), dim3(v.WG), args, 0, stream);
     if (rc == SF_OK && v.redo) {

@@ -1073,9 +1073,26 @@ def test_narrow_pass_hand_over(sf, R):
 # (R, S, T) whose lag is not split by stages, so that it takes the 32-bit pass
 # and its hand-over: odd and even partly filled tiles, full ones, both shapes
 # past 16384 ranks; the last ones with more steps than workgroups hand over
-LAG_HAND_OVER = [(4099, 2, 430), (4100, 2, 430), (8191, 2, 270), (8192, 3, 270), (8193, 2, 240), (16383, 2, 135),
-                 (16384, 3, 135), (16387, 3, 5), (16388, 2, 300), (32768, 2, 3), (4097, 1, 2070), (4098, 1, 4150),
+LAG_HAND_OVER = [(4099, 2, 520), (4100, 2, 520), (8191, 2, 520), (8192, 3, 520), (8193, 2, 260), (16383, 2, 260),
+                 (16384, 3, 260), (16387, 3, 5), (16388, 2, 300), (32768, 2, 3), (4097, 1, 2070), (4098, 1, 4150),
                  (16385, 1, 2060)]
+
+
+@pytest.mark.parametrize("R,S,T", [(4099, 2, 200), (4100, 5, 150), (6001, 5, 140), (8191, 3, 260), (8192, 3, 300),
+                                   (8193, 3, 129), (8193, 5, 60), (16383, 2, 129), (16384, 3, 129), (16384, 5, 64)])
+def test_lag_of_few_steps(sf, R, S, T):
+    """Past 4096 ranks a few steps in one launch, their stages shared or not:
+    ties, values past 2^32 in every third step, one that spans 2^46."""
+    rng = np.random.Generator(np.random.PCG64(R + 7 * S))
+    d = rng.integers(0, 10**7, size=(T, S, R), dtype=np.int64)
+    d[1::4] //= 10**6
+    d[::3, S - 1] += rng.integers(0, 2**33, size=R, dtype=np.int64)
+    d[T - 1, 0, R - 1] = 2**46
+    lag, inc = sf.sf_frontier_lag(torch.from_numpy(d).to(DEV))
+    torch.cuda.synchronize()
+    want_lag, want_inc = oracle.frontier_lag(d)
+    np.testing.assert_array_equal(lag.cpu().numpy(), want_lag)
+    np.testing.assert_array_equal(inc.cpu().numpy(), want_inc)
 
 
 @pytest.mark.parametrize("R,S,T", LAG_HAND_OVER)

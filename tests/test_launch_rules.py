@@ -179,3 +179,22 @@ def test_hand_over_grid_meets_no_short_period(recorder):
     for c, ls in zip(cases, launches(recorder, cases)):
         steps, redo = ls[0].grid, ls[1]
         assert redo.grid < steps and math.gcd(redo.grid, 210) == 1, (c, ls)
+
+
+@pytest.mark.parametrize("R,S,T,groups,size", [
+    (4098, 1, 500, 1, 512), (4099, 2, 512, 1, 512), (4140, 8, 48, 4, 512), (4140, 8, 160, 3, 512), (4140, 8, 256, 2, 512),
+    (4140, 4, 160, 1, 512), (6001, 8, 160, 3, 512), (6001, 8, 200, 1, 512), (8190, 8, 256, 1, 512), (8192, 12, 1, 12, 512),
+    (8193, 7, 220, 1, 1024), (10000, 8, 160, 1, 1024), (10000, 12, 48, 4, 1024), (16384, 12, 128, 2, 1024), (16384, 2, 1, 1, 1024),
+    (16384, 12, 256, 1, 1024)])
+def test_lag_of_few_steps(recorder, R, S, T, groups, size):
+    """Past 4096 ranks a few steps are one launch of one round: the stages
+    shared where two workgroups or more have a CU, else 64 bits and no
+    hand-over."""
+    (ls,) = launches(recorder, [("sf_frontier_lag", R, S, T, 1)])[0]
+    assert (ls.grid, ls.block) == (T * groups, size) and not is_narrow(ls.name), ls
+
+
+@pytest.mark.parametrize("R,T", [(8192, 513), (5001, 513), (8193, 257), (16384, 257)])
+def test_lag_of_more_steps_than_a_round(recorder, R, T):
+    ls = launches(recorder, [("sf_frontier_lag", R, 4, T, 1)])[0]
+    assert len(ls) == 2 and is_narrow(ls[0].name), ls
