@@ -291,7 +291,7 @@ __global__ __launch_bounds__(WG) void k_exposure_gain_wide(
 // overlaps the one before.
 //
 // Bound: HBM, the totals pass.  Measured on MI355X: 1024 ranks x 132 stages x
-// 1000 steps 1278 -> 188 us, 4096 x 12 x 5000 315 -> 295 us against the
+// 1000 steps 1264 -> 183 us, 4096 x 12 x 5000 315 -> 295 us against the
 // kernels that took these shapes before; 12000 x 12 x 2777 535 -> 489 us and
 // 16384 x 12 x 2034 492 -> 483 us against a radix search over the totals for
 // a bound with at least 32 ranks above it (which also needed a barrier per

@@ -764,7 +764,7 @@ LagVariant lag_shape(int R, bool split, bool in_one = false)
     if constexpr (PREFIX) {
         if (split) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false, false, false, true>(), WG, nullptr, 0};
     }
-    if constexpr (K == 16 && WG >= 512 && PREFIX) {
+    if constexpr (K == 16 && (WG >= 512 || !PREFIX)) {
         if (in_one) return LagVariant{lag_kernel<PREFIX, VEC, K, WG, false>(), WG, nullptr, 0};
     }
     if constexpr (K == 16 && (WG >= 512 || !PREFIX)) {
@@ -790,9 +790,9 @@ LagVariant pick_lag(int64_t T, int R, bool split, bool in_one)
     if (R <= 128) return lag_shape<PREFIX, VEC, 2, 64>(R, split);
     if (R <= 256) return lag_shape<PREFIX, VEC, 4, 64>(R, split);
     if (R <= 512) return lag_shape<PREFIX, VEC, 8, 64>(R, split);
-    if (R <= 1024) return lag_shape<PREFIX, VEC, 16, 64>(R, split);
-    if (R <= 2048) return lag_shape<PREFIX, VEC, 16, 128>(R, split);
-    if (R <= 4096) return lag_shape<PREFIX, VEC, 16, 256>(R, split);
+    if (R <= 1024) return lag_shape<PREFIX, VEC, 16, 64>(R, split, in_one);
+    if (R <= 2048) return lag_shape<PREFIX, VEC, 16, 128>(R, split, in_one);
+    if (R <= 4096) return lag_shape<PREFIX, VEC, 16, 256>(R, split, in_one);
     if (R <= 8192) return lag_shape<PREFIX, VEC, 16, 512>(R, split, in_one);
     if (R <= 16384) return lag_shape<PREFIX, VEC, 16, 1024>(R, split, in_one);
     return lag_wide<PREFIX, VEC>(T, R);  // R <= SF_MAX_R
@@ -826,13 +826,16 @@ static int64_t lag_units(int64_t T, int R, int S)
     return std::max<int64_t>(1, std::min<int64_t>(units, S));
 }
 
-// A step's stages by one workgroup, in 64 bits, in one round: past 4096 ranks
-// the 32-bit pass gains nothing there, and the launch behind it costs 2 us
-// (10000 ranks x 2 x 220 18.5 -> 15.5 us, 4140 x 1 x 100 8.6 -> 6.5, 12001 x 8 x 256
-// 71 -> 67).
-static bool lag_in_one(int64_t T, int R)
+// Steps (rows) that all run at once, 16 waves per CU: the 64-bit shapes take
+// them, past 512 ranks, since the 32-bit pass gains nothing there and the launch
+// behind it costs 1 to 2 us (the lag: 10000 ranks x 2 x 220 18.5 -> 15.5 us, 4140 x
+// 1 x 100 8.6 -> 6.5, 12001 x 8 x 256 71 -> 67; rows of the raw spread: 700 ranks x
+// 200 9.7 -> 8.1, 4096 13.6 -> 12.6, 6000 15.7 : 17.6; 3918 x 1024 13.7 -> 12.3, 1500
+// 16.5 : 17.6; 12000 x 256 12.9 -> 11.6, 400 17.9 : 19.7).
+static bool one_round(int64_t T, int R)
 {
-    return R > 4096 && R <= 16384 && T <= (R <= 8192 ? 2 : 1) * kLagCUs;
+    const int waves = R <= 1024 ? 1 : R <= 2048 ? 2 : R <= 4096 ? 4 : R <= 8192 ? 8 : 16;
+    return R <= 16384 && T <= kLagCUs * 16 / waves;
 }
 
 // Waves below which the raw spread takes rows for steps.
@@ -860,11 +863,12 @@ static int launch_lag(const int64_t* d, int64_t T, int R, int S, int64_t* out, i
         units = lag_units(T, R, S);
         SC = (int)((S + units - 1) / units);
         units = (S + SC - 1) / SC;
-        in_one = units == 1 && lag_in_one(T, R);
+        in_one = units == 1 && one_round(T, R);
     } else if ((waves < kSpreadWaves || R > 4096 || (R <= 512 && waves <= kSpreadWaves * 3 / 2)) &&
                T <= INT32_MAX / S) {
         T *= S;
         S = SC = 1;
+        in_one = one_round(T, R);
     }
     const bool vec2 = (R & 1) == 0;
     const LagVariant v = vec2 ? pick_lag<PREFIX, 2>(T, R, units > 1, in_one) : pick_lag<PREFIX, 1>(T, R, units > 1, in_one);

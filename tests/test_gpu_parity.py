@@ -1045,10 +1045,9 @@ def test_lag_rank_sweep(sf, R):
 
 @pytest.mark.parametrize("R", [1024, 2048, 4096, 8192, 16384])
 def test_narrow_pass_hand_over(sf, R):
-    """At 1024 to 16384 ranks the raw spread runs on 32-bit values and hands a
-    row whose values leave 32 bits to the 64-bit kernel; the lag of so few
-    steps shares their stages among workgroups, in 64 bits (its own hand-over:
-    test_lag_hand_over):
+    """At 1024 to 16384 ranks, so few steps that the 64-bit shapes take them
+    (rows for the raw spread, the stages shared among workgroups for the lag; the
+    32-bit passes' hand-over: test_lag_hand_over, test_spread_hand_over):
     a duration of 2^32 or more, a rebased prefix that carries past 2^32 at
     a later stage, an overflow at the last stage only, neighbours that stay
     narrow, and every step handed over; all against the oracle."""
@@ -1120,10 +1119,13 @@ def test_lag_hand_over(sf, R, S, T):
 
 
 @pytest.mark.parametrize("R,S,T", [(513, 6, 800), (513, 8, 1300), (514, 1, 4200), (1023, 7, 1250), (1025, 6, 700),
-                                   (2047, 5, 2100), (4097, 6, 360), (16385, 2, 1100)])
+                                   (2047, 5, 2100), (4097, 6, 360), (16385, 2, 1100), (1024, 5, 900), (2048, 3, 700),
+                                   (2049, 2, 600), (4095, 2, 600), (4096, 3, 350), (8191, 3, 180), (8192, 3, 180),
+                                   (8193, 2, 130), (16383, 2, 130), (16384, 2, 130)])
 def test_spread_hand_over(sf, R, S, T):
-    """The raw spread's hand-over with more marked rows or steps than it has
-    workgroups: one long stage in every step, then rows marked at random."""
+    """The raw spread's hand-over, where its rows are more than run at once (at
+    513 to 4097 and 16385 ranks with more marked ones than workgroups): one long
+    stage in every step, then rows marked at random."""
     rng = np.random.Generator(np.random.PCG64(R * 5 + S))
     d = rng.integers(0, 10**7, size=(T, S, R), dtype=np.int64)
     d[:, S // 2] += 5 * 10**9

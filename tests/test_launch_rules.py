@@ -198,3 +198,13 @@ def test_lag_of_few_steps(recorder, R, S, T, groups, size):
 def test_lag_of_more_steps_than_a_round(recorder, R, T):
     ls = launches(recorder, [("sf_frontier_lag", R, 4, T, 1)])[0]
     assert len(ls) == 2 and is_narrow(ls[0].name), ls
+
+
+@pytest.mark.parametrize("R,rows", [(513, 4096), (1024, 4096), (1025, 2048), (2048, 2048), (2049, 1024), (4096, 1024), (4097, 512),
+                                    (8192, 512), (8193, 256), (16383, 256), (16384, 256)])
+def test_spread_of_few_rows(recorder, R, rows):
+    """Rows that all run at once take the 64-bit shapes and hand nothing over."""
+    cases = [("sf_rank_spread", R, S, T, 100) for S, T in ((1, rows), (4, rows // 4), (1, rows + 1), (4, rows // 4 + 1))]
+    names = [[k.name for k in ls] for ls in launches(recorder, cases)]
+    assert [is_narrow(n[0]) for n in names] == [False, False, True, True], names
+    assert [len(n) for n in names] == [2, 2, 3, 3], names
