@@ -734,8 +734,8 @@ const void* lag_kernel()
 // 128 and 16384 ranks; 12-13% slower for the lag's PUBU shapes at 1024 and
 // 4096 ranks, whose register allocation grows past 96, so those keep the
 // tests).  NARROW (32-bit values, two workgroups per CU) for the raw spread
-// at 16 values per lane and for the lag where a step holds 8 or more waves
-// (measured at 16384 ranks: 32% faster for the raw spread, 18% for the lag;
+// at 16 values per lane and for the lag where a step holds 8 or more waves,
+// unless all steps run at once (one_round) (measured at 16384 ranks: 32% faster for the raw spread, 18% for the lag;
 // at 1024 and 4096 ranks the raw spread 9% and 4% faster, the lag 6% slower,
 // so the lag keeps its 64-bit shapes there).
 // More than 16384 ranks: up to 32768 the 32-bit pass with 32 values per lane,
