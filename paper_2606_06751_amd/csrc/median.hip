@@ -250,13 +250,16 @@ __global__ __launch_bounds__(kMedWG) __attribute__((amdgpu_waves_per_eu(W == 1 ?
     auto load = [&](int64_t w, int64_t c0) {
         const int n = rows_of(w);
         const int64_t cc = c0 + c < C - 2 ? c0 + c : C - 2;
-        // the wave's rows of a sweep, from the tile's first column on, through
-        // a buffer resource that ends after row n - 1: slots past the window
-        // read 0 without a branch or memory traffic
-        const char* q = reinterpret_cast<const char*>(d + (w * window + wrow) * C + c0);
-        const uint32_t off = (uint32_t)(((i0 - wrow) * C + cc - c0) * 8);  // below 2^32: the host checks
+        // the wave's rows of a sweep through a buffer resource that ends
+        // after row n - 1: slots past the window read 0 without a branch or
+        // memory traffic.  A wave of one row or less has it start at the
+        // tile's first column, which bounds its offsets at any C; the others
+        // are 3-6% slower so (4096 ranks x 12 x 5000, windows of 250 348 : 361 us)
+        const int64_t cb = PARTS <= 4 ? c0 : 0;
+        const char* q = reinterpret_cast<const char*>(d + (w * window + wrow) * C + cb);
+        const uint32_t off = (uint32_t)(((i0 - wrow) * C + cc - cb) * 8);  // below 2^32: the host checks
         const int64_t step = (int64_t)RPS * C * 8;
-        int64_t left = ((n - wrow) * C - c0) * 8;
+        int64_t left = ((n - wrow) * C - cb) * 8;
 #pragma unroll
         for (int j = 0; j < NSW; ++j) {
             const int over = (int)(left >> 32);  // compared by halves: the scalar unit has no 64-bit order
@@ -445,7 +448,7 @@ __global__ __launch_bounds__(kMedLongWG) void k_window_median_long(const int64_t
 
 struct MedianVariant {
     const void* fn;
-    int cols;   // columns per tile
+    int cols;  // columns per tile
     int64_t most;  // columns C whose rows of one wave lie within 32-bit offsets
 };
 
@@ -454,7 +457,7 @@ MedianVariant median_variant()
 {
     // a wave's load takes PARTS / 4 rows, or a part of one
     return MedianVariant{reinterpret_cast<const void*>(&k_window_median<PARTS, W>), kMedWG / PARTS,
-                         PARTS <= 4 ? INT64_MAX : (int64_t)(UINT32_MAX / 8 / (PARTS / 4)) - 1};
+                         PARTS <= 4 ? INT64_MAX : (int64_t)(UINT32_MAX / 8 / (PARTS / 4))};
 }
 
 // By the longest window's steps.  Past 512 steps W = 2: twice the columns per
